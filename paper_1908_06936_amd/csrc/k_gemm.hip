@@ -95,7 +95,7 @@ __global__ __launch_bounds__(256, 2) void k_panel_trsm(double* __restrict__ Dk, 
   double* C = panel_tile(Dk, below, i, k, ts) + u * BLK + (int64_t)c * BLK * ts;
   v4d acc[4][4];
   acc_zero(acc);
-  gemm_blk<false, false>(C, ts, dinv, BLK, BLK, acc, sm);
+  gemm_blk<false, true>(C, ts, dinv, BLK, BLK, acc, sm);  // Bop(n, q) = X(n, q), X row by row
   acc_store(C, ts, acc, 1.0, false);
 }
 
@@ -113,7 +113,7 @@ __global__ __launch_bounds__(256, 2) void k_dinv_right(double* __restrict__ Xd, 
   const double* D = dinv + (k * T + c) * BLK * BLK;
   v4d acc[4][4];
   acc_zero(acc);
-  gemm_blk<false, true>(C, ts, D, BLK, BLK, acc, sm);  // Bop(n, q) = D(q, n)
+  gemm_blk<false, false>(C, ts, D, BLK, BLK, acc, sm);  // Bop(n, q) = X(q, n), X row by row
   acc_store(C, ts, acc, -1.0, false);
 }
 
@@ -143,7 +143,7 @@ __global__ __launch_bounds__(256, 2) void k_dinv_left(double* __restrict__ Xd, c
   const double* D = dinv + (k * T + c) * BLK * BLK;
   v4d acc[4][4];
   acc_zero(acc);
-  gemm_blk<false, true>(D, BLK, C, ts, BLK, acc, sm);  // Aop(m, q) = D(m, q), Bop(n, q) = C(q, n)
+  gemm_blk<true, true>(D, BLK, C, ts, BLK, acc, sm);  // Aop(m, q) = X(m, q), X row by row; Bop(n, q) = C(q, n)
   acc_store(C, ts, acc, 1.0, false);
 }
 

@@ -144,167 +144,278 @@ __global__ void k_scatter(const double* __restrict__ v, const int32_t* __restric
   if (i < n) out[perm[i]] = v[i];
 }
 
-// sqrt(d) and 1 / sqrt(d) from the hardware reciprocal square root and two
-// Newton steps (each doubles the correct bits: y <- y + y (1 - d y^2) / 2),
-// then one Newton step on the square root itself (s <- s + (d - s^2) / (2 s));
-// within an ulp or two of the correctly rounded values, without the long
-// correctly rounded sequences on the factorisation's serial path.
-__device__ __forceinline__ void sqrt_and_rsqrt(double d, double* sq, double* rsq) {
-  double y = __builtin_amdgcn_rsq(d);
-#pragma unroll
-  for (int it = 0; it < 2; ++it) {
-    const double e = fma(-d * y, y, 1.0);
-    y = fma(0.5 * y, e, y);
-  }
-  const double s0 = d * y;
-  *sq = fma(0.5 * y, fma(-s0, s0, d), s0);
-  *rsq = y;
+// ------------------------------------------------ diagonal 128-block factor
+// 1 / sqrt(d) from the hardware reciprocal square root (good to about 2^-24)
+// and one third-order step y <- y + y e (1/2 + 3/8 e), e = 1 - d y^2, whose
+// error is below e^3 ~ 2^-69: within an ulp or two of the rounded value.
+__device__ __forceinline__ double rsqrt_ulp(double d) {
+  const double y = __builtin_amdgcn_rsq(d);
+  const double e = fma(-d * y, y, 1.0);
+  return fma(y * e, fma(0.375, e, 0.5), y);
 }
 
-// ------------------------------------------------ diagonal 128-block factor
-// Cholesky of one 128 x 128 block and the inverse of its factor.
-// 256 threads; thread (tr, tc) = (t % 16, t / 16) holds the 64 entries
-// (tr + 16 p, tc + 16 q) in registers.
-//   factor (right-looking, one barrier per column): the owners of column j
-//   publish it to LDS, then every thread applies A_rc -= A_rj A_cj / A_jj to
-//   its entries with r, c > j and the owners keep L_rj = A_rj / sqrt(A_jj).
-//   inverse: L goes to LDS; with T = unit lower triangular, rows m = 0..127:
-//   the owners of row m publish it and T_ij -= (L_im / L_mm) T_mj for i > m >= j;
-//   then X = L^-1 has X_ij = T_ij / L_ii.
-// Writes L (zeros above the diagonal) over the block, X to dinv (ld 128), the
-// block's sum of 2 ln L_jj to *ldpart and the first failing global column
-// (1-based) to *info with an atomic minimum.
-__global__ __launch_bounds__(256) void k_potrf_blk(double* __restrict__ A, int64_t lda, double* __restrict__ dinv,
-                                                   double* __restrict__ ldpart, unsigned long long* __restrict__ info,
-                                                   int64_t col0) {
-  // L packed by columns (lower triangle only): L_rc at lcol(c) + r - c.  The
-  // block needs 69 KB of LDS, so it fits on a CU beside one trailing-update
-  // block and the lookahead panel is not starved by the update.
-  __shared__ double Ls[BLK * (BLK + 1) / 2];
-  __shared__ double pub[2][BLK];  // published column (factor) / row (inverse)
-  __shared__ double dg[BLK];      // L_jj
-  __shared__ double idg[BLK];     // 1 / L_jj
-  const int t = threadIdx.x, tr = t & 15, tc = t >> 4;
-  double a[8][8];
+// 1 / d likewise: y + y (e + e^2), e = 1 - d y
+__device__ __forceinline__ double rcp_ulp(double d) {
+  const double y = __builtin_amdgcn_rcp(d);
+  const double e = fma(-d, y, 1.0);
+  return fma(y, fma(e, e, e), y);
+}
+
+// f(integral_constant<int, I>) for I = B, ..., E - 1
+template <int B, int E, class F>
+__device__ __forceinline__ void static_for(F f) {
+  if constexpr (B < E) {
+    f(std::integral_constant<int, B>{});
+    static_for<B + 1, E>(f);
+  }
+}
+
+// Lane L of each row of 16 lanes, in every lane of the row (DPP row_newbcast,
+// the form that double-precision instructions take).  A DPP source must not be
+// written by one of the two instructions before; the compiler does not see
+// into the block, hence the s_nop.
+template <int L>
+__device__ __forceinline__ double row_bcast(double v) {
+  double r;
+  asm("s_nop 1\n\tv_mov_b64_dpp %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf" : "=v"(r) : "v"(v), "n"(L));
+  return r;
+}
+
+// g[I] += bcast_I(p) gv, u[I] += bcast_I(p) uv for the rows I, ..., I + N - 1
+// (N = 1 or 4), the broadcast folded into the multiply-add
+template <int I, int N>
+__device__ __forceinline__ void row_axpy(double p, double gv, double uv, double* g, double* u) {
+#define EXG_AXPY(G, U, L)                                                       \
+  "v_fmac_f64_dpp " G ", %[p], %[gv] row_newbcast:" L " row_mask:0xf bank_mask:0xf\n\t" \
+  "v_fmac_f64_dpp " U ", %[p], %[uv] row_newbcast:" L " row_mask:0xf bank_mask:0xf\n\t"
+  if constexpr (N == 4) {
+    asm("s_nop 1\n\t" EXG_AXPY("%0", "%1", "%[i0]") EXG_AXPY("%2", "%3", "%[i1]") EXG_AXPY("%4", "%5", "%[i2]")
+            EXG_AXPY("%6", "%7", "%[i3]")
+        : "+v"(g[I]), "+v"(u[I]), "+v"(g[I + 1]), "+v"(u[I + 1]), "+v"(g[I + 2]), "+v"(u[I + 2]), "+v"(g[I + 3]),
+          "+v"(u[I + 3])
+        : [p] "v"(p), [gv] "v"(gv), [uv] "v"(uv), [i0] "n"(I), [i1] "n"(I + 1), [i2] "n"(I + 2), [i3] "n"(I + 3));
+  } else {
+    static_assert(N == 1, "one row or four");
+    asm("s_nop 1\n\t" EXG_AXPY("%0", "%1", "%[i0]")
+        : "+v"(g[I]), "+v"(u[I])
+        : [p] "v"(p), [gv] "v"(gv), [uv] "v"(uv), [i0] "n"(I));
+  }
+#undef EXG_AXPY
+}
+
+// the same for the rows B, ..., E - 1
+template <int B, int E>
+__device__ __forceinline__ void rows_axpy(double p, double gv, double uv, double* g, double* u) {
+  if constexpr (E - B >= 4) {
+    row_axpy<B, 4>(p, gv, uv, g, u);
+    rows_axpy<B + 4, E>(p, gv, uv, g, u);
+  } else if constexpr (B < E) {
+    row_axpy<B, 1>(p, gv, uv, g, u);
+    rows_axpy<B + 1, E>(p, gv, uv, g, u);
+  }
+}
+
+// barrier of a workgroup that exchanges data through LDS only: global stores
+// in flight are not waited for
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// Cholesky of one 128 x 128 block and the inverse of its factor, by 16-wide
+// steps k = 0..7 of row elimination on [A | I].  With A = L L^T, d_j = L_jj^2
+// and X = L^-1, row j of the eliminated panel holds sqrt(d_j) L_cj in the
+// columns c > j and sqrt(d_j) X_jc in the columns c <= j: the rows stay
+// unscaled, so the serial chain of pivots needs no square root.
+//   The 36 lower 16 x 16 blocks live in LDS.  Slot (r, c) holds A(r, c)^T until
+//   step c consumes it and then T(r, c), the running right-hand side that
+//   becomes X(r, c); the eliminated row panel k is kept in P.  Both halves of
+//   the elimination share one update on MFMA, with P_c = 16 columns c of P:
+//     A(r, c)^T -= P_c^T D^-1 P_r  (c > k),   T(r, c) -= P_r^T D^-1 P_c  (c <= k).
+//   Waves 0 and 1 eliminate a row panel as one instruction stream with lanes
+//   as columns: every lane carries one of the 128 panel columns and, in each
+//   row of 16 lanes, a copy of the diagonal block's columns, so pivots and
+//   multipliers are broadcast within 16 lanes by DPP moves, without LDS.
+//   While they eliminate panel k, waves 2, 3, 6 and 7 (the SIMDs without an
+//   eliminating wave) finish step k - 1's update and waves 4 and 5 write panel
+//   k - 1, scaled, to global memory; between eliminations the eight waves bring
+//   the eight blocks of the next panel up to date.
+// What bounds it is the chain of 128 pivots (broadcast, reciprocal, multiply-adds,
+// the update of the next row: about 260 cycles each) and, in the first steps,
+// the latency of the updates beside it.  The LDS (94 KB) and 128 registers per
+// lane leave room for one trailing-update workgroup on the same CU.  It takes
+// 32 us alone and 47 / 101 us on average in the factorisations of n = 10,000 /
+// 22,500, where a form with one barrier per column (255 in all) took 99 us
+// alone and 123 / 225 us.
+// Writes L (zeros above the diagonal) over the block, X row by row to dinv
+// (X(r, c) at 128 r + c, the order in which the panels leave LDS), the block's
+// sum of 2 ln L_jj to *ldpart and the first failing global column
+// (1-based) to *info with an atomic minimum.  The strict upper part of the
+// input does not enter the result.
+constexpr int PB = 16;           // step width
+constexpr int PNB = BLK / PB;    // steps
+constexpr int PLD = BLK + PB + 2;  // row panel: 128 columns, then its 16 x 16 diagonal block; the stride keeps
+                                   // reads along its rows and its columns nearly free of bank conflicts
+constexpr int PSLOT = PB * PB;
+constexpr int POTRF_LDS = (PNB * (PNB + 1) / 2 * PSLOT + PB * PLD + 6 * PB + BLK) * 8;  // bytes
+// The LDS is dynamic so that the compiler keeps to 128 registers per lane: two
+// waves per SIMD then fit beside a trailing-update workgroup's two.
+__global__ __launch_bounds__(512, 4) void k_potrf_blk(
+    double* __restrict__ A, int64_t lda, double* __restrict__ dinv, double* __restrict__ ldpart,
+    unsigned long long* __restrict__ info, int64_t col0) {
+  extern __shared__ double potrf_lds[];
+  double* slots = potrf_lds;
+  double* P = slots + PNB * (PNB + 1) / 2 * PSLOT;
+  double* nrd = P + PB * PLD;  // -1 / d_j of the panels k (even, odd; a copy per eliminating wave)
+  double* rsc = nrd + 4 * PB;  // 1 / L_jj (a copy per writing wave)
+  double* piv = rsc + 2 * PB;  // d_j
+  const int t = threadIdx.x;
+  int lane = t & 63, l16 = lane & 15, q16 = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+  auto slot = [&](int r, int c) { return slots + (r * (r + 1) / 2 + c) * PSLOT; };
+  {
+    v4d v[5];
+    int r = 0, c = 0, rs[5], cs[5];
 #pragma unroll
-  for (int p = 0; p < 8; ++p)
+    for (int s = 0; s < 5; ++s) {
+      const int b = min(8 * s + w, PNB * (PNB + 1) / 2 - 1);  // spare turns repeat the last block
+      while ((r + 1) * (r + 2) / 2 <= b) ++r;
+      c = b - r * (r + 1) / 2;
+      rs[s] = r;
+      cs[s] = c;
+      const double* Ab = A + PB * r + (int64_t)(PB * c) * lda;
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int r = tr + 16 * p, c = tc + 16 * q;
-      a[p][q] = (r >= c) ? A[r + (int64_t)c * lda] : 0.0;
+      for (int q = 0; q < 4; ++q) v[s][q] = Ab[l16 + (4 * q + q16) * lda];
     }
-  // j = 16 qj + jj: the block index qj is a compile-time constant in each
-  // unrolled copy, so the owners address their registers statically
 #pragma unroll
-  for (int qj = 0; qj < 8; ++qj) {
+    for (int s = 0; s < 5; ++s)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) slot(rs[s], cs[s])[(4 * q + q16) * PB + l16] = v[s][q];
+  }
+  // step k's update of block (r, c), r > k; T(r, k) starts here, from zero
+  auto upd_load = [&](int r, int c, int k, v4d& acc, v4d& x, v4d& y) {
+    const int cx = c > k ? c : r, cy = c > k ? r : c;
+    const double* S = slot(r, c);
+    const double* nd = nrd + 2 * PB * (k & 1);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int row = 4 * q + q16;
+      x[q] = P[row * PLD + PB * cx + l16] * nd[row];
+      y[q] = P[row * PLD + PB * cy + l16];
+      acc[q] = S[row * PB + l16];
+    }
+  };
+  auto upd_store = [&](int r, int c, const v4d& acc) {
+    double* S = slot(r, c);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) S[(4 * q + q16) * PB + l16] = acc[q];
+  };
 #pragma unroll 1
-    for (int jj = 0; jj < 16; ++jj) {
-      const int j = 16 * qj + jj;
-      const int buf = j & 1;
-      if (tc == jj) {
+  for (int k = 0;; ++k) {
+    // addresses are formed anew in each step, not kept in registers across them
+    asm volatile("" : "+v"(lane), "+v"(l16), "+v"(q16));
+    lds_barrier();  // panel k's blocks are up to date with step k - 1
+    if (w < 2) {
+      if (k == PNB) break;
+      const int col = 64 * w + lane, cb = col >> 4;
+      const double* src = cb > k ? slot(cb, k) : slot(k, cb);
+      const double* dsrc = slot(k, k);
+      double* nd = nrd + 2 * PB * (k & 1) + PB * w;
+      double u[PB], g[PB];  // the lane's panel column, its copy of a diagonal column
 #pragma unroll
-        for (int p = 0; p < 8; ++p) {
-          const int r = tr + 16 * p;
-          if (r >= j) pub[buf][r] = a[p][qj];
+      for (int j = 0; j < PB; ++j) {
+        g[j] = dsrc[j * PB + l16];
+        u[j] = cb == k ? (l16 == j ? 1.0 : 0.0) : src[j * PB + l16];
+      }
+      static_for<0, PB>([&](auto jc) {
+        constexpr int j = decltype(jc)::value;
+        const double d = row_bcast<j>(g[j]);
+        const double r = -rcp_ulp(d), gv = g[j] * r, uv = u[j] * r;  // -row j / d_j
+        nd[j] = r;
+        if constexpr (j + 1 < PB) {
+          row_axpy<j + 1, 1>(g[j], gv, uv, g, u);  // the next pivot's row first
+          rows_axpy<j + 2, PB>(g[j], gv, uv, g, u);
+        }
+      });
+      lds_barrier();  // nobody reads panel k - 1 any more
+#pragma unroll
+      for (int j = 0; j < PB; ++j) P[j * PLD + col] = u[j];
+      if (col < PB) {
+#pragma unroll
+        for (int j = 0; j < PB; ++j) P[j * PLD + BLK + col] = g[j];
+      }
+    } else if (w == 4 || w == 5) {
+      if (k > 0) {  // panel k - 1 to global memory
+        const int col = 64 * (w - 4) + lane, cb = col >> 4;
+        const double pv = P[l16 * PLD + BLK + l16], sd = sqrt(pv);  // pivot l16
+        double* rs = rsc + PB * (w - 4);
+        rs[l16] = rsqrt_ulp(pv);
+        const int d = col - PB * (k - 1);  // > j below the diagonal
+        double* Ak = A + PB * (k - 1) * lda + col;
+        double* X = dinv + PB * (k - 1) * BLK + col;
+        // L takes its diagonal block's columns from the panel's tail
+        const double* Pc = P + (cb == k - 1 ? BLK + l16 : col);
+#pragma unroll
+        for (int j = 0; j < PB; ++j) {
+          const double rj = rs[j], v = Pc[j * PLD] * rj, x = P[j * PLD + col] * rj;
+          Ak[(uint32_t)j * (uint32_t)lda] = d > j ? v : (d == j ? sd : 0.0);
+          X[j * BLK] = cb < k ? x : 0.0;
+        }
+        if (cb == k - 1) {
+          piv[col] = pv;
+          if (!(pv > 0.0) || !(pv <= DBL_MAX)) atomicMin(info, (unsigned long long)(col0 + col + 1));
         }
       }
-      __syncthreads();
-      const double d = pub[buf][j];
-      double sd, isd;
-      sqrt_and_rsqrt(d, &sd, &isd);
-      if (t == 0) {
-        dg[j] = sd;
-        idg[j] = isd;
-        if (!(d > 0.0) || !(d <= DBL_MAX)) atomicMin(info, (unsigned long long)(col0 + j + 1));
-      }
-      const double id = isd * isd;
-      double lr[8], lc[8];
+      if (k == PNB) break;
+      lds_barrier();
+    } else {
+      if (k == PNB) break;
+      // the rest of step k - 1: rows r > k, columns c <= r except k (r of them),
+      // dealt to the four waves in turn and taken two at a time
+      int r = k + 1, e = (w & 1) + 2 * (w >> 2);
+      auto next = [&](int* rr, int* cc) {
+        while (e >= r && r < PNB) e -= r++;
+        *rr = r;
+        *cc = e + (e >= k);
+        e += 4;
+        return r < PNB;
+      };
+      int r0, c0, r1, c1;
+#pragma unroll 1
+      while (k > 0 && next(&r0, &c0)) {
+        const bool two = next(&r1, &c1);
+        if (!two) r1 = r0, c1 = c0;
+        v4d a0, x0, y0, a1, x1, y1;
+        upd_load(r0, c0, k - 1, a0, x0, y0);
+        upd_load(r1, c1, k - 1, a1, x1, y1);
+        asm volatile("" : "+v"(a0), "+v"(a1));  // loaded in any case: a branch per element costs more
+        if (c0 == k - 1) a0 = (v4d){0.0, 0.0, 0.0, 0.0};
+        if (c1 == k - 1) a1 = (v4d){0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int p = 0; p < 8; ++p) {
-        const int r = tr + 16 * p;
-        lr[p] = (r > j) ? pub[buf][r] : 0.0;
-      }
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const int c = tc + 16 * q;
-        lc[q] = (c > j) ? pub[buf][c] * id : 0.0;
-      }
-#pragma unroll
-      for (int q = qj; q < 8; ++q) {
-        // lower blocks only: the upper ones are never read
-#pragma unroll
-        for (int p = q; p < 8; ++p) a[p][q] -= lr[p] * lc[q];
-      }
-      if (tc == jj) {
-#pragma unroll
-        for (int p = qj; p < 8; ++p) {
-          const int r = tr + 16 * p;
-          if (r > j) a[p][qj] = pub[buf][r] * isd;
-          else if (r == j) a[p][qj] = sd;
+        for (int q = 0; q < 4; ++q) {
+          a0 = mfma64(x0[q], y0[q], a0);
+          a1 = mfma64(x1[q], y1[q], a1);
         }
+        upd_store(r0, c0, a0);
+        if (two) upd_store(r1, c1, a1);
       }
+      lds_barrier();
+    }
+    lds_barrier();  // panel k eliminated
+    if (k < PNB - 1) {  // the blocks of panel k + 1, one per wave
+      const int r = w <= k + 1 ? k + 1 : w, c = w <= k + 1 ? w : k + 1;
+      v4d a, x, y;
+      upd_load(r, c, k, a, x, y);
+      asm volatile("" : "+v"(a));
+      if (c == k) a = (v4d){0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int q = 0; q < 4; ++q) a = mfma64(x[q], y[q], a);
+      upd_store(r, c, a);
     }
   }
-  // L to LDS and to the block (zeros above the diagonal)
-#pragma unroll
-  for (int p = 0; p < 8; ++p)
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int r = tr + 16 * p, c = tc + 16 * q;
-      const double lv = (r >= c) ? a[p][q] : 0.0;
-      if (r >= c) Ls[c * BLK - c * (c - 1) / 2 + r - c] = lv;
-      A[r + (int64_t)c * lda] = lv;
-      a[p][q] = 0.0;  // now T, strictly lower part
-    }
-  __syncthreads();
-#pragma unroll
-  for (int pm = 0; pm < 8; ++pm) {
-#pragma unroll 1
-    for (int mm = 0; mm < 16; ++mm) {
-      const int m = 16 * pm + mm;
-      if (m == BLK - 1) break;
-      const int buf = m & 1;
-      if (tr == mm) {
-#pragma unroll
-        for (int q = 0; q <= pm; ++q) {
-          const int c = tc + 16 * q;
-          if (c < m) pub[buf][c] = a[pm][q];
-        }
-        if (tc == 0) pub[buf][m] = 1.0;
-      }
-      __syncthreads();
-      const double inv_lmm = idg[m];
-      double li[8], tm[8];
-#pragma unroll
-      for (int p = pm; p < 8; ++p) {
-        const int r = tr + 16 * p;
-        li[p] = (r > m) ? Ls[m * BLK - m * (m - 1) / 2 + r - m] * inv_lmm : 0.0;
-      }
-#pragma unroll
-      for (int q = 0; q <= pm; ++q) {
-        const int c = tc + 16 * q;
-        tm[q] = (c <= m) ? pub[buf][c] : 0.0;
-      }
-#pragma unroll
-      for (int p = pm; p < 8; ++p)
-#pragma unroll
-        for (int q = 0; q <= pm; ++q) a[p][q] -= li[p] * tm[q];
-    }
+  // 2 sum ln L_jj = sum ln d_j, in a fixed order
+  lds_barrier();
+  if (w == 0) {
+    const double s = wave_sum(log(piv[lane]) + log(piv[64 + lane]));
+    if (t == 0) *ldpart = s;
   }
-#pragma unroll
-  for (int p = 0; p < 8; ++p)
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int r = tr + 16 * p, c = tc + 16 * q;
-      const double il = idg[r];
-      dinv[r + c * BLK] = (r > c) ? a[p][q] * il : ((r == c) ? il : 0.0);
-    }
-  // 2 sum ln L_jj: one logarithm per thread, fixed-order block sum (pub is
-  // free once every thread has left the inverse loop)
-  __syncthreads();
-  double lg[1] = {t < BLK ? 2.0 * log(dg[t]) : 0.0};
-  block_sum<1>(lg, &pub[0][0]);
-  if (t == 0) *ldpart = lg[0];
 }
 
 // ------------------------------------------------------- triangular solves
@@ -506,13 +617,13 @@ __global__ void k_copy_diag_lower(double* __restrict__ dst, const double* __rest
   dst[e] = (r >= c) ? diag[k * tt + q] : 0.0;
 }
 
-// dst[k] block (c, c) = dinv[k][c] for every diagonal tile k
+// dst[k] block (c, c) = dinv[k][c] (stored row by row) for every diagonal tile k
 __global__ void k_put_dinv(double* __restrict__ dst, const double* __restrict__ dinv, int64_t ts, int64_t NT, int c) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= NT * BLK * BLK) return;
   const int T = (int)(ts / BLK);
   const int64_t k = e / (BLK * BLK), q = e % (BLK * BLK);
-  const int r = (int)(q % BLK), cc = (int)(q / BLK);
+  const int cc = (int)(q % BLK), r = (int)(q / BLK);
   dst[k * ts * ts + (int64_t)c * BLK + r + ((int64_t)c * BLK + cc) * ts] = dinv[(k * T + c) * BLK * BLK + q];
 }
 
@@ -542,7 +653,7 @@ void launch_scatter(const double* v, const int32_t* perm, int64_t n, double* out
 
 void launch_potrf_blk(double* A, int64_t lda, double* dinv, double* ldpart, unsigned long long* info, int64_t col0,
                       hipStream_t s) {
-  hipLaunchKernelGGL(k_potrf_blk, dim3(1), dim3(256), 0, s, A, lda, dinv, ldpart, info, col0);
+  hipLaunchKernelGGL(k_potrf_blk, dim3(1), dim3(512), POTRF_LDS, s, A, lda, dinv, ldpart, info, col0);
 }
 
 void launch_trsv_fwd(const TileMat& M, const double* Xd, int64_t nreal, double* rhs, double* y, hipStream_t s) {

@@ -1,0 +1,49 @@
+"""Kernel variants at the sizes where their blocks begin and end, against the
+CPU oracle.  Tolerances are those of test_gpu_parity.py: l relative 1e-10 and
+the score 1e-8 of each component plus its rounding floor."""
+import numpy as np
+import pytest
+
+import inputgen
+from scorecheck import assert_score_close
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def dev(a):
+    return torch.as_tensor(np.ascontiguousarray(a, dtype=np.float64), device="cuda")
+
+
+@pytest.fixture(scope="module")
+def exa():
+    import paper_1908_06936_amd as exa
+
+    return exa
+
+
+# the 128 x 128 factor works in 16-wide steps: below, at and above one step,
+# the last step, a whole block and the first rows of the next block
+@pytest.mark.parametrize("n", [2, 15, 16, 17, 33, 112, 113, 127, 128, 129, 145])
+def test_block_factor_step_edges(orc, exa, n):
+    ctx = exa.Context(ts=128)
+    x, y = inputgen.uniform(n, seed=100 + n)
+    th = [1.2, 0.1, 0.9]
+    z = orc.simulate(x, y, th, inputgen.normals(n, seed=n))
+    ll_ref, g_ref = orc.loglik_grad(x, y, z, th)
+    ll, g = ctx.loglik_grad(dev(x), dev(y), dev(z), th)
+    assert ll == pytest.approx(ll_ref, rel=1e-10)
+    assert_score_close(g, g_ref, n, th)
+
+
+@pytest.mark.parametrize("pos", [1, 15, 16, 40, 112, 127, 128, 140])
+def test_block_factor_reports_the_first_failed_pivot(exa, pos):
+    # points on a line far apart (the covariance underflows to the identity
+    # times sigma^2 = 4) except for two that coincide, so the second of the two
+    # is the one failing pivot (4 - (4 / 2)^2 = 0 exactly), in Z-order column pos
+    n = 150
+    x = np.arange(n, dtype=np.float64) * 1000.0
+    x[pos] = x[pos - 1]
+    ctx = exa.Context(ts=256)
+    st, ll, info = ctx.loglik_status(dev(x), dev(np.zeros(n)), dev(np.ones(n)), [4.0, 0.1, 0.5])
+    assert st == exa.ENOTPD and ll == -np.inf and info == pos + 1
