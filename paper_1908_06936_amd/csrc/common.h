@@ -10,7 +10,8 @@
 //     adds nothing to log det Sigma or to z^T Sigma^-1 z (padded z = 0).
 //   * Every dense product is cut into 128 x 128 output blocks, one per
 //     256-thread workgroup (4 wave64s in a 2 x 2 arrangement, each owning a
-//     64 x 64 sub-block = 4 x 4 MFMA tiles of 16 x 16).
+//     64 x 64 sub-block = 4 x 4 MFMA tiles of 16 x 16), or into 64- or 32-wide
+//     ones where 128 x 128 blocks would leave the chip idle (block_tiles).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -24,6 +25,8 @@ constexpr int BK = 16;          // k-depth of one LDS stage
 constexpr int LDP = BLK + 2;    // padded LDS row length (doubles)
 constexpr int GEMM_THREADS = 256;
 constexpr int GEMM_LDS = 2 * 2 * BK * LDP;  // doubles: 2 operands x 2 stages
+// LDS of a (32 MI) x (32 NI) output block
+constexpr int gemm_lds(int MI, int NI) { return 2 * BK * (32 * MI + 2 + 32 * NI + 2); }
 
 typedef double v4d __attribute__((ext_vector_type(4)));
 typedef double d2 __attribute__((ext_vector_type(2)));
@@ -150,8 +153,9 @@ __device__ __forceinline__ gbyte* uniform_base(const void* p) {
   return (gbyte*)(((uint64_t)hi << 32) | lo);
 }
 
-// One 128 x 128 block of  sum_k Aop(m, k) Bop(n, k)  accumulated into acc,
-// over a virtual k range [0, K) that may run across several tiles.
+// One (32 MI) x (32 NI) block of  sum_k Aop(m, k) Bop(n, k)  accumulated into
+// acc, over a virtual k range [0, K) that may run across several tiles.  The
+// order of the products does not depend on MI and NI (128 x 128 when both are 4).
 //   aptr(k0) returns the address of Aop(0, k0) for a stage starting at k0;
 //   within a stage (BK consecutive k):
 //     Aop(m, k0 + q) = aptr(k0)[m + q * lda]   (AKC = false, m contiguous)
@@ -159,110 +163,125 @@ __device__ __forceinline__ gbyte* uniform_base(const void* p) {
 //   bptr / Bop(n, k) likewise with ldb, BKC.
 // The operands may be FP64 or FP32 (aptr / bptr return const double* or
 // const float*; FP32 values are widened exactly).  K must be a multiple of
-// 2 BK; every pair of elements read must be aligned to its size.  acc[i][j] holds output rows m = wr*64 + 16 i + (lane & 15) and
-// columns n = wc*64 + 16 j + 4 r + (lane >> 4), r = 0..3 (wr = wave >> 1,
+// 2 BK; every pair of elements read must be aligned to its size.  acc[i][j] holds output rows m = wr*16 MI + 16 i + (lane & 15) and
+// columns n = wc*16 NI + 16 j + 4 r + (lane >> 4), r = 0..3 (wr = wave >> 1,
 // wc = wave & 1); with this assignment the lanes of one store instruction
 // write 16 consecutive rows of a column-major output.
 // SB = true: each stage's operand addresses are aptr(k0) / bptr(k0), which must
 // then be the same in every lane, held in scalar registers plus one 32-bit byte
 // offset per thread and load (so 127 lda + 15 elements must stay below 4 GiB);
 // this frees about 14 vector registers.  SB = false: 64-bit vector addresses.
-template <bool AKC, bool BKC, bool SB = false, class AP, class BP>
-__device__ __forceinline__ void gemm_core(AP aptr, int64_t lda, BP bptr, int64_t ldb, int K, v4d (&acc)[4][4],
+template <bool AKC, bool BKC, bool SB = false, int MI = 4, int NI = 4, class AP, class BP>
+__device__ __forceinline__ void gemm_core(AP aptr, int64_t lda, BP bptr, int64_t ldb, int K, v4d (&acc)[MI][NI],
                                           double* sm) {
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int wr = w >> 1, wc = w & 1;
   double* sA = sm;
-  double* sB = sm + 2 * BK * LDP;
+  constexpr int LA = 32 * MI + 2, LB = 32 * NI + 2;  // padded LDS rows
+  constexpr int PA = 16 * MI, PBn = 16 * NI;         // element pairs per row
+  double* sB = sm + 2 * BK * LA;
   using TA = std::remove_cv_t<std::remove_pointer_t<decltype(aptr(0))>>;
   using TB = std::remove_cv_t<std::remove_pointer_t<decltype(bptr(0))>>;
   // two register sets: the global loads run two stages ahead of the MFMAs
-  Pair2<TA> ra0[4], ra1[4];
-  Pair2<TB> rb0[4], rb1[4];
-  uint32_t oa[4], ob[4];  // SB: byte offsets of the thread's pairs within a stage
+  Pair2<TA> ra0[MI], ra1[MI];
+  Pair2<TB> rb0[NI], rb1[NI];
+  uint32_t oa[MI], ob[NI];  // SB: byte offsets of the thread's pairs within a stage
 #pragma unroll
-  for (int s = 0; s < 4; ++s) {
+  for (int s = 0; s < MI; ++s) {
     const int idx = t + GEMM_THREADS * s;
     oa[s] = (uint32_t)(sizeof(TA) * (AKC ? 2 * (idx & 7) + (int64_t)(idx >> 3) * lda
-                                         : 2 * (idx & 63) + (int64_t)(idx >> 6) * lda));
-    ob[s] = (uint32_t)(sizeof(TB) * (BKC ? 2 * (idx & 7) + (int64_t)(idx >> 3) * ldb
-                                         : 2 * (idx & 63) + (int64_t)(idx >> 6) * ldb));
+                                         : 2 * (idx % PA) + (int64_t)(idx / PA) * lda));
   }
-  auto gload = [&](int k0, Pair2<TA> (&ra)[4], Pair2<TB> (&rb)[4]) {
+#pragma unroll
+  for (int s = 0; s < NI; ++s) {
+    const int idx = t + GEMM_THREADS * s;
+    ob[s] = (uint32_t)(sizeof(TB) * (BKC ? 2 * (idx & 7) + (int64_t)(idx >> 3) * ldb
+                                         : 2 * (idx % PBn) + (int64_t)(idx / PBn) * ldb));
+  }
+  auto gload = [&](int k0, Pair2<TA> (&ra)[MI], Pair2<TB> (&rb)[NI]) {
     if constexpr (SB) {
       gbyte* A = uniform_base(aptr(k0));
       gbyte* B = uniform_base(bptr(k0));
 #pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        ra[s].load_g(A + oa[s]);
-        rb[s].load_g(B + ob[s]);
+      for (int s = 0; s < (MI > NI ? MI : NI); ++s) {
+        if (s < MI) ra[s].load_g(A + oa[s]);
+        if (s < NI) rb[s].load_g(B + ob[s]);
       }
       return;
     }
     const TA* A = aptr(k0);
     const TB* B = bptr(k0);
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
+    for (int s = 0; s < (MI > NI ? MI : NI); ++s) {
       const int idx = t + GEMM_THREADS * s;
-      if (!AKC) {
-        const int kk = idx >> 6, m2 = idx & 63;
-        ra[s].load(A + 2 * m2 + (int64_t)kk * lda);
-      } else {
-        const int m = idx >> 3, kp = idx & 7;
-        ra[s].load(A + 2 * kp + (int64_t)m * lda);
+      if (s < MI) {
+        if (!AKC) {
+          const int kk = idx / PA, m2 = idx % PA;
+          ra[s].load(A + 2 * m2 + (int64_t)kk * lda);
+        } else {
+          const int m = idx >> 3, kp = idx & 7;
+          ra[s].load(A + 2 * kp + (int64_t)m * lda);
+        }
       }
-      if (!BKC) {
-        const int kk = idx >> 6, n2 = idx & 63;
-        rb[s].load(B + 2 * n2 + (int64_t)kk * ldb);
-      } else {
-        const int n = idx >> 3, kp = idx & 7;
-        rb[s].load(B + 2 * kp + (int64_t)n * ldb);
+      if (s < NI) {
+        if (!BKC) {
+          const int kk = idx / PBn, n2 = idx % PBn;
+          rb[s].load(B + 2 * n2 + (int64_t)kk * ldb);
+        } else {
+          const int n = idx >> 3, kp = idx & 7;
+          rb[s].load(B + 2 * kp + (int64_t)n * ldb);
+        }
       }
     }
   };
-  auto sstore = [&](int buf, const Pair2<TA> (&ra)[4], const Pair2<TB> (&rb)[4]) {
-    double* a = sA + buf * BK * LDP;
-    double* b = sB + buf * BK * LDP;
+  auto sstore = [&](int buf, const Pair2<TA> (&ra)[MI], const Pair2<TB> (&rb)[NI]) {
+    double* a = sA + buf * BK * LA;
+    double* b = sB + buf * BK * LB;
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
+    for (int s = 0; s < (MI > NI ? MI : NI); ++s) {
       const int idx = t + GEMM_THREADS * s;
-      const d2 va = ra[s].get(), vb = rb[s].get();
-      if (!AKC) {
-        const int kk = idx >> 6, m2 = idx & 63;
-        *(d2*)(a + kk * LDP + 2 * m2) = va;
-      } else {
-        const int m = idx >> 3, kp = idx & 7;
-        a[(2 * kp) * LDP + m] = va.x;
-        a[(2 * kp + 1) * LDP + m] = va.y;
+      if (s < MI) {
+        const d2 va = ra[s].get();
+        if (!AKC) {
+          const int kk = idx / PA, m2 = idx % PA;
+          *(d2*)(a + kk * LA + 2 * m2) = va;
+        } else {
+          const int m = idx >> 3, kp = idx & 7;
+          a[(2 * kp) * LA + m] = va.x;
+          a[(2 * kp + 1) * LA + m] = va.y;
+        }
       }
-      if (!BKC) {
-        const int kk = idx >> 6, n2 = idx & 63;
-        *(d2*)(b + kk * LDP + 2 * n2) = vb;
-      } else {
-        const int n = idx >> 3, kp = idx & 7;
-        b[(2 * kp) * LDP + n] = vb.x;
-        b[(2 * kp + 1) * LDP + n] = vb.y;
+      if (s < NI) {
+        const d2 vb = rb[s].get();
+        if (!BKC) {
+          const int kk = idx / PBn, n2 = idx % PBn;
+          *(d2*)(b + kk * LB + 2 * n2) = vb;
+        } else {
+          const int n = idx >> 3, kp = idx & 7;
+          b[(2 * kp) * LB + n] = vb.x;
+          b[(2 * kp + 1) * LB + n] = vb.y;
+        }
       }
     }
   };
   auto compute = [&](int cur) {
-    const double* a = sA + cur * BK * LDP + wr * 64 + (lane & 15);
-    const double* b = sB + cur * BK * LDP + wc * 64 + (lane & 15);
+    const double* a = sA + cur * BK * LA + wr * 16 * MI + (lane & 15);
+    const double* b = sB + cur * BK * LB + wc * 16 * NI + (lane & 15);
 #pragma unroll
     for (int kk = 0; kk < BK; kk += 4) {
-      const int ko = (kk + (lane >> 4)) * LDP;
-      double af[4], bf[4];
+      const int ka = (kk + (lane >> 4)) * LA, kb = (kk + (lane >> 4)) * LB;
+      double af[MI], bf[NI];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) af[i] = a[ko + 16 * i];
+      for (int i = 0; i < MI; ++i) af[i] = a[ka + 16 * i];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) bf[j] = b[ko + 16 * j];
+      for (int j = 0; j < NI; ++j) bf[j] = b[kb + 16 * j];
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < MI; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = mfma64(bf[j], af[i], acc[i][j]);
+        for (int j = 0; j < NI; ++j) acc[i][j] = mfma64(bf[j], af[i], acc[i][j]);
     }
   };
-  const int nst = K / BK;  // even: every K here is a multiple of 128
+  const int nst = K / BK;  // even: every K here is a multiple of 32
   gload(0, ra0, rb0);
   gload(BK, ra1, rb1);
   sstore(0, ra0, rb0);
@@ -283,12 +302,12 @@ __device__ __forceinline__ void gemm_core(AP aptr, int64_t lda, BP bptr, int64_t
 
 // gemm_core over one contiguous operand pair:
 //   Aop(m, k) = A[m + k lda] (AKC = false) or A[k + m lda] (AKC = true), same for B.
-template <bool AKC, bool BKC, bool SB = false>
+template <bool AKC, bool BKC, bool SB = false, int MI = 4, int NI = 4>
 __device__ __forceinline__ void gemm_blk(const double* __restrict__ A, int64_t lda, const double* __restrict__ B,
-                                         int64_t ldb, int K, v4d (&acc)[4][4], double* sm) {
+                                         int64_t ldb, int K, v4d (&acc)[MI][NI], double* sm) {
   auto ap = [=](int k0) { return AKC ? A + k0 : A + (int64_t)k0 * lda; };
   auto bp = [=](int k0) { return BKC ? B + k0 : B + (int64_t)k0 * ldb; };
-  gemm_core<AKC, BKC, SB>(ap, lda, bp, ldb, K, acc, sm);
+  gemm_core<AKC, BKC, SB, MI, NI>(ap, lda, bp, ldb, K, acc, sm);
 }
 
 // Workgroups are dispatched to the 8 XCDs in turn (workgroup b to XCD b mod 8),
@@ -305,33 +324,35 @@ __device__ __forceinline__ int64_t xcd_block(int64_t nb) {
   return b < nb ? b : -1;
 }
 
-__device__ __forceinline__ void acc_zero(v4d (&acc)[4][4]) {
+template <int MI, int NI>
+__device__ __forceinline__ void acc_zero(v4d (&acc)[MI][NI]) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < MI; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = (v4d){0.0, 0.0, 0.0, 0.0};
+    for (int j = 0; j < NI; ++j) acc[i][j] = (v4d){0.0, 0.0, 0.0, 0.0};
 }
 
-// C(m, n) = beta * C(m, n) + alpha * acc  on a column-major 128 x 128 block.
-// With beta = 1 the 16 values of one accumulator row group are all loaded
+// C(m, n) = beta * C(m, n) + alpha * acc  on a column-major (32 MI) x (32 NI)
+// block.  With beta = 1 the values of one accumulator row group are all loaded
 // before any is stored: the compiler cannot tell that the computed addresses
 // differ, and would otherwise wait for each load's round trip in turn.
-__device__ __forceinline__ void acc_store(double* C, int64_t ldc, const v4d (&acc)[4][4], double alpha, bool beta1) {
+template <int MI, int NI>
+__device__ __forceinline__ void acc_store(double* C, int64_t ldc, const v4d (&acc)[MI][NI], double alpha, bool beta1) {
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int wr = w >> 1, wc = w & 1;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int m = wr * 64 + 16 * i + (lane & 15);
-    double* p = C + m + (int64_t)(wc * 64 + (lane >> 4)) * ldc;
-    double old[4][4];
+  for (int i = 0; i < MI; ++i) {
+    const int m = wr * 16 * MI + 16 * i + (lane & 15);
+    double* p = C + m + (int64_t)(wc * 16 * NI + (lane >> 4)) * ldc;
+    double old[NI][4];
     if (beta1) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
+      for (int j = 0; j < NI; ++j)
 #pragma unroll
         for (int r = 0; r < 4; ++r) old[j][r] = p[(int64_t)(16 * j + 4 * r) * ldc];
     }
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < NI; ++j)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const double v = alpha * acc[i][j][r];

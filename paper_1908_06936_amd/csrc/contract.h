@@ -26,32 +26,33 @@ __device__ __forceinline__ void contract_entry(int64_t gi, int64_t gj, double xi
   g3[2] += f * d2;
 }
 
-// FP64 accumulators in the layout of gemm_core (rows m = wr*64 + 16 i +
-// (lane & 15), columns n = wc*64 + 16 j + 4 r + (lane >> 4)); row0 / col0 are
-// the global indices of the block's first row and column.  The 16 values of
+// FP64 accumulators in the layout of gemm_core (rows m = wr*16 MI + 16 i +
+// (lane & 15), columns n = wc*16 NI + 16 j + 4 r + (lane >> 4)); row0 / col0 are
+// the global indices of the block's first row and column.  The 4 NI values of
 // one row group go through thread-private LDS slots so that the loop over
 // them indexes at run time without forcing the accumulators out of registers.
-__device__ __forceinline__ void contract_block64(const v4d (&acc)[4][4], int64_t row0, int64_t col0, int64_t nreal,
+template <int MI, int NI>
+__device__ __forceinline__ void contract_block64(const v4d (&acc)[MI][NI], int64_t row0, int64_t col0, int64_t nreal,
                                                  const double* __restrict__ xs, const double* __restrict__ ys,
                                                  const double* __restrict__ av, const double* __restrict__ qt,
-                                                 const double* __restrict__ cst, double* sm /* >= 16 x 256 */,
+                                                 const double* __restrict__ cst, double* sm /* >= 4 NI x 256 */,
                                                  double* out) {
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int wr = w >> 1, wc = w & 1;
   double g3[3] = {0.0, 0.0, 0.0};
   double* fb = sm;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < MI; ++i) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < NI; ++j)
 #pragma unroll
       for (int r = 0; r < 4; ++r) fb[(j * 4 + r) * GEMM_THREADS + t] = acc[i][j][r];
-    const int64_t gi = row0 + wr * 64 + 16 * i + (lane & 15);
+    const int64_t gi = row0 + wr * 16 * MI + 16 * i + (lane & 15);
     if (gi >= nreal) continue;
     const double xi = xs[gi], yi = ys[gi], ai = av[gi];
-    for (int e = 0; e < 16; ++e) {
+    for (int e = 0; e < 4 * NI; ++e) {
       const int j = e >> 2, r = e & 3;
-      const int64_t gj = col0 + wc * 64 + 16 * j + 4 * r + (lane >> 4);
+      const int64_t gj = col0 + wc * 16 * NI + 16 * j + 4 * r + (lane >> 4);
       if (gj >= nreal || gj > gi) continue;
       contract_entry(gi, gj, xi, yi, ai, fb[e * GEMM_THREADS + t], xs, ys, av, qt, cst, g3);
     }

@@ -672,7 +672,8 @@ exageo_status gradient(exageo_ctx* c, const Plan& p) {
   double* rhs = at<double>(c, p.off_av);
   double* av = at<double>(c, p.off_alpha);
   double* Xd = at<double>(c, p.off_xd);
-  int64_t nparts = exg::lauum_blocks(p.ts, p.NT);  // partial triples of the contraction
+  int64_t nparts = 0;  // partial triples of the contraction
+  double* part = at<double>(c, p.off_part);
   const int64_t tt = p.ts * p.ts, half = std::max<int64_t>(1, p.NT - 1) * tt;
   // a = Sigma^-1 z = L^-T y (already there, refined, in mixed precision with
   // refinement steps)
@@ -700,7 +701,7 @@ exageo_status gradient(exageo_ctx* c, const Plan& p) {
     nparts = exg::launch_lauum_contract_lp(M, tag, p.n, at<double>(c, p.off_xs), at<double>(c, p.off_ys), av,
                                            at<double>(c, p.off_qt), at<double>(c, p.off_cst),
                                            at<int32_t>(c, p.off_bli), at<int32_t>(c, p.off_blj), c->bfirst[p.NT],
-                                           at<double>(c, p.off_part), c->stream);
+                                           part, c->stream);
   } else {
     exg::launch_trsv_bwd(M, Xd, rhs, av, c->stream);
     // L^-1 in place, then the fused LAUUM + contraction
@@ -710,11 +711,14 @@ exageo_status gradient(exageo_ctx* c, const Plan& p) {
         [&](int64_t k, hipStream_t s) { exg::launch_trtri_right(M, Xd + k * tt, P64 + (k & 1) * half, k, p.n, s); },
         [&](int64_t k, hipStream_t s) { exg::launch_trtri_rest(M, Xd + k * tt, P64 + (k & 1) * half, k, p.n, s); });
     if (st) return st;
-    exg::launch_lauum_contract(M, p.n, at<double>(c, p.off_xs), at<double>(c, p.off_ys), av,
-                               at<double>(c, p.off_qt), at<double>(c, p.off_cst), at<double>(c, p.off_part),
-                               c->stream);
+    // the staging buffer is free again and holds the partial triples of any
+    // block size: 2 (NT - 1) ts^2 doubles (2 ts^2 for one tile) against
+    // 3 (NT (NT + 1) / 2) (ts / 32)^2
+    part = P64;
+    nparts = exg::launch_lauum_contract(M, p.n, at<double>(c, p.off_xs), at<double>(c, p.off_ys), av,
+                                        at<double>(c, p.off_qt), at<double>(c, p.off_cst), part, c->stream);
   }
-  exg::launch_finalize_grad(at<double>(c, p.off_part), nparts, at<double>(c, p.off_out) + 3, c->stream);
+  exg::launch_finalize_grad(part, nparts, at<double>(c, p.off_out) + 3, c->stream);
   HIPCHK(c, hipGetLastError());
   rec(c, 5);
   return EXAGEO_OK;

@@ -30,11 +30,14 @@ namespace exg {
 // Mixed precision runs it only on its FP64 targets: the diagonal tiles
 // (PAIRS_DIAG) and the FP64 band tiles, given as a list of (i, j) entries
 // off, off + 1, ... (PAIRS_LIST; stored in the band pool).
+// Block edge 32 B (block_tiles); T = ts / (32 B) blocks per tile edge.
+template <int B>
 __global__ __launch_bounds__(256, 2) void k_chol_update(TileMat M, const double* __restrict__ below, int T, int64_t k,
                                                         int64_t nreal, int64_t nb, int mode, int64_t off,
                                                         const int32_t* __restrict__ li,
                                                         const int32_t* __restrict__ lj) {
-  __shared__ double sm[GEMM_LDS];
+  constexpr int E = 32 * B;
+  __shared__ double sm[gemm_lds(B, B)];
   const int64_t ts = M.ts;
   const int64_t b = blockIdx.x;
   if (b >= nb) return;
@@ -50,18 +53,18 @@ __global__ __launch_bounds__(256, 2) void k_chol_update(TileMat M, const double*
   }
   const int64_t i = k + 1 + a, j = k + 1 + c;
   if (i == j && u < v) return;
-  if (i * ts + u * BLK >= nreal || j * ts + v * BLK >= nreal) return;  // padding: update is zero
-  const double* A = below + a * ts * ts + u * BLK;
-  const double* B = below + c * ts * ts + v * BLK;
-  double* C = ((i == j || !M.pool) ? tptr(M, i, j) : band64(M, off_index(i, j, M.NT))) + u * BLK +
-              (int64_t)v * BLK * ts;
-  v4d acc[4][4];
+  if (i * ts + u * E >= nreal || j * ts + v * E >= nreal) return;  // padding: update is zero
+  const double* Ap = below + a * ts * ts + u * E;
+  const double* Bp = below + c * ts * ts + v * E;
+  double* C = ((i == j || !M.pool) ? tptr(M, i, j) : band64(M, off_index(i, j, M.NT))) + u * E +
+              (int64_t)v * E * ts;
+  v4d acc[B][B];
   acc_zero(acc);
-  gemm_blk<false, false, true>(A, ts, B, ts, (int)ts, acc, sm);
+  gemm_blk<false, false, true, B, B>(Ap, ts, Bp, ts, (int)ts, acc, sm);
   acc_store(C, ts, acc, -1.0, true);
 }
 
-// panel k, sub-column c: rows g0 + blockIdx.x (128-row blocks, global index)
+// panel k, sub-column c: rows g0 + ... (128-row blocks, global index)
 //   C = A[g, c] -= A[g, 0:c] A[(k,c), 0:c]^T
 // The panel of column k is the diagonal tile Dk followed by the contiguous
 // FP64 tiles `below`; row block g (global index) lies in tile i = g / T.
@@ -69,145 +72,164 @@ __device__ __forceinline__ double* panel_tile(double* Dk, double* below, int64_t
   return i == k ? Dk : below + (i - k - 1) * ts * ts;
 }
 
+// one (32 B) x (32 B) part of a 128 x 128 block per workgroup
+template <int B>
 __global__ __launch_bounds__(256, 2) void k_panel_update(double* __restrict__ Dk, double* __restrict__ below,
                                                          int64_t ts, int T, int64_t k, int c, int64_t g0) {
-  __shared__ double sm[GEMM_LDS];
-  const int64_t g = g0 + blockIdx.x;
+  constexpr int E = 32 * B, S = 4 / B;  // S x S parts per block
+  __shared__ double sm[gemm_lds(B, B)];
+  const int64_t g = g0 + blockIdx.x / (S * S);
+  const int q = (int)(blockIdx.x % (S * S)), pu = q / S, pv = q % S;
   const int64_t i = g / T;
   const int u = (int)(g % T);
-  double* P = panel_tile(Dk, below, i, k, ts) + u * BLK;
-  const double* D = Dk + c * BLK;
-  v4d acc[4][4];
+  double* P = panel_tile(Dk, below, i, k, ts) + u * BLK + pu * E;
+  const double* D = Dk + c * BLK + pv * E;
+  v4d acc[B][B];
   acc_zero(acc);
-  gemm_blk<false, false, true>(P, ts, D, ts, c * BLK, acc, sm);
-  acc_store(P + (int64_t)c * BLK * ts, ts, acc, -1.0, true);
+  gemm_blk<false, false, true, B, B>(P, ts, D, ts, c * BLK, acc, sm);
+  acc_store(P + (int64_t)(c * BLK + pv * E) * ts, ts, acc, -1.0, true);
 }
 
 // panel k, sub-column c: C = A[g, c] Dinv_c^T for the blocks below the diagonal
-// block (in place: each workgroup reads only the block it overwrites)
+// block, 32 B rows of a block per workgroup (in place: each workgroup reads
+// only the rows that it overwrites)
+template <int B>
 __global__ __launch_bounds__(256, 2) void k_panel_trsm(double* __restrict__ Dk, double* __restrict__ below, int64_t ts,
                                                        int T, int64_t k, int c, int64_t g0,
                                                        const double* __restrict__ dinv) {
-  __shared__ double sm[GEMM_LDS];
-  const int64_t g = g0 + blockIdx.x;
+  constexpr int E = 32 * B, S = 4 / B;
+  __shared__ double sm[gemm_lds(B, 4)];
+  const int64_t g = g0 + blockIdx.x / S;
   const int64_t i = g / T;
   const int u = (int)(g % T);
-  double* C = panel_tile(Dk, below, i, k, ts) + u * BLK + (int64_t)c * BLK * ts;
-  v4d acc[4][4];
+  double* C = panel_tile(Dk, below, i, k, ts) + u * BLK + (int)(blockIdx.x % S) * E + (int64_t)c * BLK * ts;
+  v4d acc[B][4];
   acc_zero(acc);
-  gemm_blk<false, true>(C, ts, dinv, BLK, BLK, acc, sm);  // Bop(n, q) = X(n, q), X row by row
+  gemm_blk<false, true, false, B, 4>(C, ts, dinv, BLK, BLK, acc, sm);  // Bop(n, q) = X(n, q), X row by row
   acc_store(C, ts, acc, 1.0, false);
 }
 
 // ------------------------------------------- inverses of the diagonal tiles
 // All NT diagonal tiles at once, on copies Xd[k] (ts x ts) that start as the
 // lower part of L_kk; step c of the 128-block algorithm.
-// right: X[r, c] <- -X[r, c] Dinv_c for r > c
+// right: X[r, c] <- -X[r, c] Dinv_c for r > c, 32 B rows per workgroup (in place)
+template <int B>
 __global__ __launch_bounds__(256, 2) void k_dinv_right(double* __restrict__ Xd, const double* __restrict__ dinv,
                                                        int64_t ts, int T, int c) {
-  __shared__ double sm[GEMM_LDS];
-  const int nr = T - 1 - c;
+  constexpr int E = 32 * B, S = 4 / B;
+  __shared__ double sm[gemm_lds(B, 4)];
+  const int nr = (T - 1 - c) * S;
   const int64_t k = blockIdx.x / nr;
-  const int r = c + 1 + (int)(blockIdx.x % nr);
-  double* C = Xd + k * ts * ts + r * BLK + (int64_t)c * BLK * ts;
+  const int r = (int)(blockIdx.x % nr);
+  double* C = Xd + k * ts * ts + (c + 1) * BLK + r * E + (int64_t)c * BLK * ts;
   const double* D = dinv + (k * T + c) * BLK * BLK;
-  v4d acc[4][4];
+  v4d acc[B][4];
   acc_zero(acc);
-  gemm_blk<false, false>(C, ts, D, BLK, BLK, acc, sm);  // Bop(n, q) = X(q, n), X row by row
+  gemm_blk<false, false, false, B, 4>(C, ts, D, BLK, BLK, acc, sm);  // Bop(n, q) = X(q, n), X row by row
   acc_store(C, ts, acc, -1.0, false);
 }
 
-// gemm: X[r, b] += X[r, c] X[c, b] for r > c > b
+// gemm: X[r, b] += X[r, c] X[c, b] for r > c > b, on (32 B) x (32 B) blocks
+template <int B>
 __global__ __launch_bounds__(256, 2) void k_dinv_gemm(double* __restrict__ Xd, int64_t ts, int T, int c) {
-  __shared__ double sm[GEMM_LDS];
-  const int nr = T - 1 - c;
-  const int per = nr * c;
+  constexpr int E = 32 * B, S = 4 / B;
+  __shared__ double sm[gemm_lds(B, B)];
+  const int nc = c * S, per = (T - 1 - c) * S * nc;
   const int64_t k = blockIdx.x / per;
   const int q = (int)(blockIdx.x % per);
-  const int r = c + 1 + q / c, bb = q % c;
+  const int64_t r = (c + 1) * BLK + (q / nc) * E, bb = (int64_t)(q % nc) * E;
   double* X = Xd + k * ts * ts;
-  v4d acc[4][4];
+  v4d acc[B][B];
   acc_zero(acc);
-  gemm_blk<false, true>(X + r * BLK + (int64_t)c * BLK * ts, ts, X + c * BLK + (int64_t)bb * BLK * ts, ts, BLK, acc,
-                        sm);
-  acc_store(X + r * BLK + (int64_t)bb * BLK * ts, ts, acc, 1.0, true);
+  gemm_blk<false, true, false, B, B>(X + r + (int64_t)c * BLK * ts, ts, X + c * BLK + bb * ts, ts, BLK, acc, sm);
+  acc_store(X + r + bb * ts, ts, acc, 1.0, true);
 }
 
-// left: X[c, b] <- Dinv_c X[c, b] for b < c (in place)
+// left: X[c, b] <- Dinv_c X[c, b] for b < c, 32 B columns per workgroup (in place)
+template <int B>
 __global__ __launch_bounds__(256, 2) void k_dinv_left(double* __restrict__ Xd, const double* __restrict__ dinv,
                                                       int64_t ts, int T, int c) {
-  __shared__ double sm[GEMM_LDS];
-  const int64_t k = blockIdx.x / c;
-  const int bb = (int)(blockIdx.x % c);
-  double* C = Xd + k * ts * ts + c * BLK + (int64_t)bb * BLK * ts;
+  constexpr int E = 32 * B, S = 4 / B;
+  __shared__ double sm[gemm_lds(4, B)];
+  const int64_t k = blockIdx.x / (c * S);
+  const int bb = (int)(blockIdx.x % (c * S));
+  double* C = Xd + k * ts * ts + c * BLK + (int64_t)bb * E * ts;
   const double* D = dinv + (k * T + c) * BLK * BLK;
-  v4d acc[4][4];
+  v4d acc[4][B];
   acc_zero(acc);
-  gemm_blk<true, true>(D, BLK, C, ts, BLK, acc, sm);  // Aop(m, q) = X(m, q), X row by row; Bop(n, q) = C(q, n)
+  // Aop(m, q) = X(m, q), X row by row; Bop(n, q) = C(q, n)
+  gemm_blk<true, true, false, 4, B>(D, BLK, C, ts, BLK, acc, sm);
   acc_store(C, ts, acc, 1.0, false);
 }
 
 // --------------------------------------------------------- tile TRTRI step k
+// Blocks of edge E = 32 B (block_tiles), T = ts / E per tile edge.
 // P_i = -A_ik X_kk for i > k, into the buffer P (tile i - k - 1); one block
-// (u, v) per workgroup, k range restricted to the non-zero rows v*128.. of the
+// (u, v) per workgroup, k range restricted to the non-zero rows v E.. of the
 // lower-triangular X_kk.
+template <int B>
 __global__ __launch_bounds__(256, 2) void k_tri_right(TileMat M, const double* __restrict__ Xk, double* __restrict__ P,
                                                       int T, int64_t k, int64_t nreal, int64_t nb) {
   const int64_t ts = M.ts;
-  __shared__ double sm[GEMM_LDS];
+  constexpr int E = 32 * B;
+  __shared__ double sm[gemm_lds(B, B)];
   const int64_t b = blockIdx.x;
   if (b >= nb) return;
   const int64_t i = k + 1 + b / (T * T);
   const int sub = (int)(b % (T * T));
   const int u = sub / T, v = sub % T;
-  const int64_t off = (int64_t)v * BLK * ts;
-  const double* A = tptr(M, i, k) + u * BLK + off;
-  double* C = P + (i - k - 1) * ts * ts + u * BLK + off;
-  v4d acc[4][4];
+  const int64_t off = (int64_t)v * E * ts;
+  const double* Ap = tptr(M, i, k) + u * E + off;
+  double* C = P + (i - k - 1) * ts * ts + u * E + off;
+  v4d acc[B][B];
   acc_zero(acc);
   // padded rows of L^-1 are zero: store zeros (the buffer is copied back whole)
-  if (i * ts + u * BLK < nreal) gemm_blk<false, true>(A, ts, Xk + v * BLK + off, ts, (int)(ts - v * BLK), acc, sm);
+  if (i * ts + u * E < nreal) gemm_blk<false, true, false, B, B>(Ap, ts, Xk + v * E + off, ts, (int)(ts - v * E), acc, sm);
   acc_store(C, ts, acc, -1.0, false);
 }
 
 // A_ij += P_i A_kj for k < i < NT, 0 <= j < k (P_i = the new A_ik)
+template <int B>
 __global__ __launch_bounds__(256, 2) void k_tri_gemm(TileMat M, const double* __restrict__ P, int T, int64_t k,
                                                      int64_t nreal, int64_t nb) {
   const int64_t ts = M.ts;
-  __shared__ double sm[GEMM_LDS];
+  constexpr int E = 32 * B;
+  __shared__ double sm[gemm_lds(B, B)];
   const int64_t b = blockIdx.x;
   if (b >= nb) return;
   const int64_t p = b / (T * T);
   const int sub = (int)(b % (T * T));
   const int u = sub / T, v = sub % T;
   const int64_t i = k + 1 + p / k, j = p % k;
-  if (i * ts + u * BLK >= nreal) return;
-  const double* A = P + (i - k - 1) * ts * ts + u * BLK;
-  const double* B = tptr(M, k, j) + (int64_t)v * BLK * ts;
-  double* C = tptr(M, i, j) + u * BLK + (int64_t)v * BLK * ts;
-  v4d acc[4][4];
+  if (i * ts + u * E >= nreal) return;
+  const double* Ap = P + (i - k - 1) * ts * ts + u * E;
+  const double* Bp = tptr(M, k, j) + (int64_t)v * E * ts;
+  double* C = tptr(M, i, j) + u * E + (int64_t)v * E * ts;
+  v4d acc[B][B];
   acc_zero(acc);
-  gemm_blk<false, true>(A, ts, B, ts, (int)ts, acc, sm);
+  gemm_blk<false, true, false, B, B>(Ap, ts, Bp, ts, (int)ts, acc, sm);
   acc_store(C, ts, acc, 1.0, true);
 }
 
 // R_j = X_kk A_kj for j < k, into the buffer P (tile j); k range restricted
-// to the non-zero columns ..(u+1)*128 of row block u of X_kk.
+// to the non-zero columns ..(u+1) E of row block u of X_kk.
+template <int B>
 __global__ __launch_bounds__(256, 2) void k_tri_left(TileMat M, const double* __restrict__ Xk, double* __restrict__ P,
                                                      int T, int64_t k, int64_t nb) {
   const int64_t ts = M.ts;
-  __shared__ double sm[GEMM_LDS];
+  constexpr int E = 32 * B;
+  __shared__ double sm[gemm_lds(B, B)];
   const int64_t b = blockIdx.x;
   if (b >= nb) return;
   const int64_t j = b / (T * T);
   const int sub = (int)(b % (T * T));
   const int u = sub / T, v = sub % T;
-  const int64_t off = (int64_t)v * BLK * ts;
-  const double* B = tptr(M, k, j) + off;
-  double* C = P + j * ts * ts + u * BLK + off;
-  v4d acc[4][4];
+  const int64_t off = (int64_t)v * E * ts;
+  const double* Bp = tptr(M, k, j) + off;
+  double* C = P + j * ts * ts + u * E + off;
+  v4d acc[B][B];
   acc_zero(acc);
-  gemm_blk<false, true>(Xk + u * BLK, ts, B, ts, (u + 1) * BLK, acc, sm);
+  gemm_blk<false, true, false, B, B>(Xk + u * E, ts, Bp, ts, (u + 1) * E, acc, sm);
   acc_store(C, ts, acc, 1.0, false);
 }
 
@@ -262,13 +284,15 @@ __global__ __launch_bounds__(256) void k_transpose_tiles(TileMat M, int64_t npt,
 // followed by g_m += sum (w_ij (a_i a_j - W_ij) / 2) dSigma_m(i, j) over its
 // entries, w = 2 below the diagonal, 1 on it, 0 above and on padding.
 // part[3 b + m] receives the block's sums (zeros for skipped blocks).
+template <int B>
 __global__ __launch_bounds__(256, 2) void k_lauum_contract(TileMat M, int T, int64_t nreal,
                                                            const double* __restrict__ xs,
                                                            const double* __restrict__ ys, const double* __restrict__ av,
                                                            const double* __restrict__ qt,
                                                            const double* __restrict__ cst, double* __restrict__ part,
                                                            int64_t nb) {
-  __shared__ double sm[GEMM_LDS];
+  constexpr int E = 32 * B;
+  __shared__ double sm[gemm_lds(B, B)];
   const int64_t ts = M.ts, NT = M.NT;
   const int64_t b = blockIdx.x;
   if (b >= nb) return;
@@ -278,20 +302,20 @@ __global__ __launch_bounds__(256, 2) void k_lauum_contract(TileMat M, int T, int
   int64_t I, J;
   tri_decode(p, &I, &J);
   // DST: dSigma is zero outside the tile band, so are those blocks' terms
-  if ((I == J && u < v) || I * ts + u * BLK >= nreal || J * ts + v * BLK >= nreal || (M.dst > 0 && I - J >= M.dst)) {
+  if ((I == J && u < v) || I * ts + u * E >= nreal || J * ts + v * E >= nreal || (M.dst > 0 && I - J >= M.dst)) {
     if (threadIdx.x < 3) part[3 * b + threadIdx.x] = 0.0;
     return;
   }
-  v4d acc[4][4];
+  v4d acc[B][B];
   acc_zero(acc);
   // One virtual k range over the tiles K = I, ..., NT-1 of tile columns I and
   // J: first rows r0.. of tile row I (X_II is lower triangular, so rows above
-  // u*128 of its column block u are zero), then every row of the tiles below.
+  // u E of its column block u are zero), then every row of the tiles below.
   // Transposed tiles: X(K, I)[k, m] sits at k ts + m of tile (K, I).  The
   // off-diagonal tiles of one tile column are stored one after another, so
   // row kk of the stack (K, I), K > I, is at kk ts of the stack's first tile
   // ((kk / ts) ts^2 + (kk % ts) ts = kk ts): no division per stage.
-  const int64_t r0 = (int64_t)u * BLK, c0 = (int64_t)v * BLK;
+  const int64_t r0 = (int64_t)u * E, c0 = (int64_t)v * E;
   const int64_t L0 = ts - r0;
   const double* XdI = M.diag + I * ts * ts;
   const double* XbI = I + 1 < NT ? (const double*)M.off + off_index(I + 1, I, NT) * ts * ts : XdI;
@@ -304,14 +328,32 @@ __global__ __launch_bounds__(256, 2) void k_lauum_contract(TileMat M, int T, int
     if (I > J) return XJ + c0 + (r0 + k0) * ts;
     return k0 < L0 ? XdI + c0 + (r0 + k0) * ts : XbI + c0 + (int64_t)(k0 - L0) * ts;
   };
-  gemm_core<false, false, true>(ap, ts, bp, ts, (int)(L0 + (NT - 1 - I) * ts), acc, sm);
+  gemm_core<false, false, true, B, B>(ap, ts, bp, ts, (int)(L0 + (NT - 1 - I) * ts), acc, sm);
   contract_block64(acc, I * ts + r0, J * ts + c0, nreal, xs, ys, av, qt, cst, sm, part + 3 * b);
 }
 
 // ------------------------------------------------------------- launchers
+#define EXG_BLOCKS(tiles, kernel, grid, stream, ...)                                                     \
+  do {                                                                                                   \
+    if ((tiles) == 4)                                                                                    \
+      hipLaunchKernelGGL(kernel<4>, dim3((unsigned)(grid)), dim3(256), 0, stream, __VA_ARGS__);          \
+    else if ((tiles) == 2)                                                                               \
+      hipLaunchKernelGGL(kernel<2>, dim3((unsigned)(grid)), dim3(256), 0, stream, __VA_ARGS__);          \
+    else                                                                                                 \
+      hipLaunchKernelGGL(kernel<1>, dim3((unsigned)(grid)), dim3(256), 0, stream, __VA_ARGS__);          \
+  } while (0)
+
+static void update_pairs(const TileMat& M, const double* below, int64_t k, int64_t nreal, int mode, int64_t off,
+                         int64_t npairs, const int32_t* li, const int32_t* lj, hipStream_t s) {
+  const int64_t T4 = M.ts / BLK;
+  const int B = block_tiles(npairs * T4 * T4);
+  const int T = (int)(M.ts / (32 * B));
+  const int64_t nblk = npairs * T * T;
+  EXG_BLOCKS(B, k_chol_update, nblk, s, M, below, T, k, nreal, nblk, mode, off, li, lj);
+}
+
 void launch_chol_update(const TileMat& M, const double* below, int64_t k, int64_t nreal, bool diag_only, int part,
                         hipStream_t s) {
-  const int T = (int)(M.ts / BLK);
   int64_t m = M.NT - k - 1;  // trailing tiles
   if (M.dst > 0 && m > M.dst - 1) m = M.dst - 1;  // DST: L_ik = 0 for i - k >= dst
   if (m <= 0) return;
@@ -329,18 +371,13 @@ void launch_chol_update(const TileMat& M, const double* below, int64_t k, int64_
     mode = PAIRS_TRI, off = 1, npairs = (m - 1) * m / 2;
   }
   if (npairs <= 0) return;
-  const int64_t nblk = npairs * T * T;
-  hipLaunchKernelGGL(k_chol_update, dim3((unsigned)nblk), dim3(256), 0, s, M, below, T, k, nreal, nblk,
-                     mode, off, (const int32_t*)nullptr, (const int32_t*)nullptr);
+  update_pairs(M, below, k, nreal, mode, off, npairs, nullptr, nullptr, s);
 }
 
 void launch_band_update(const TileMat& M, const double* below, int64_t k, int64_t nreal, const int32_t* li,
                         const int32_t* lj, int64_t e0, int64_t count, hipStream_t s) {
   if (count <= 0) return;
-  const int T = (int)(M.ts / BLK);
-  const int64_t nblk = count * T * T;
-  hipLaunchKernelGGL(k_chol_update, dim3((unsigned)nblk), dim3(256), 0, s, M, below, T, k, nreal, nblk,
-                     (int)PAIRS_LIST, e0, li, lj);
+  update_pairs(M, below, k, nreal, (int)PAIRS_LIST, e0, count, li, lj, s);
 }
 
 void launch_panel(double* Dk, double* below, int64_t ts, int64_t NT, int64_t k, int64_t nreal, double* dinv_k,
@@ -350,13 +387,17 @@ void launch_panel(double* Dk, double* below, int64_t ts, int64_t NT, int64_t k, 
   (void)NT;
   for (int c = 0; c < T; ++c) {
     const int64_t gd = k * T + c;  // global index of the diagonal block
-    if (c > 0 && gmax > gd)
-      hipLaunchKernelGGL(k_panel_update, dim3((unsigned)(gmax - gd)), dim3(256), 0, s, Dk, below, ts, T, k, c, gd);
+    if (c > 0 && gmax > gd) {
+      const int B = block_tiles(gmax - gd);
+      EXG_BLOCKS(B, k_panel_update, (gmax - gd) * (4 / B) * (4 / B), s, Dk, below, ts, T, k, c, gd);
+    }
     double* Dblk = Dk + c * BLK + (int64_t)c * BLK * ts;
     launch_potrf_blk(Dblk, ts, dinv_k + (int64_t)c * BLK * BLK, ldpart_k + c, info, gd * BLK, s);
-    if (gmax > gd + 1)
-      hipLaunchKernelGGL(k_panel_trsm, dim3((unsigned)(gmax - gd - 1)), dim3(256), 0, s, Dk, below, ts, T, k, c,
-                         gd + 1, dinv_k + (int64_t)c * BLK * BLK);
+    if (gmax > gd + 1) {
+      const int B = block_tiles(gmax - gd - 1);
+      EXG_BLOCKS(B, k_panel_trsm, (gmax - gd - 1) * (4 / B), s, Dk, below, ts, T, k, c, gd + 1,
+                 dinv_k + (int64_t)c * BLK * BLK);
+    }
   }
 }
 
@@ -364,11 +405,19 @@ void launch_diag_inverses(double* Xd, const double* diag, const double* dinv, in
   const int T = (int)(ts / BLK);
   launch_copy_diag_lower(Xd, diag, ts, NT, s);
   for (int c = 0; c < T; ++c) {
-    if (T - 1 - c > 0)
-      hipLaunchKernelGGL(k_dinv_right, dim3((unsigned)(NT * (T - 1 - c))), dim3(256), 0, s, Xd, dinv, ts, T, c);
-    if (T - 1 - c > 0 && c > 0)
-      hipLaunchKernelGGL(k_dinv_gemm, dim3((unsigned)(NT * (T - 1 - c) * c)), dim3(256), 0, s, Xd, ts, T, c);
-    if (c > 0) hipLaunchKernelGGL(k_dinv_left, dim3((unsigned)(NT * c)), dim3(256), 0, s, Xd, dinv, ts, T, c);
+    const int64_t nr = T - 1 - c;
+    if (nr > 0) {
+      const int B = block_tiles(NT * nr), S = 4 / B;
+      EXG_BLOCKS(B, k_dinv_right, NT * nr * S, s, Xd, dinv, ts, T, c);
+    }
+    if (nr > 0 && c > 0) {
+      const int B = block_tiles(NT * nr * c), S = 4 / B;
+      EXG_BLOCKS(B, k_dinv_gemm, NT * nr * c * S * S, s, Xd, ts, T, c);
+    }
+    if (c > 0) {
+      const int B = block_tiles(NT * c), S = 4 / B;
+      EXG_BLOCKS(B, k_dinv_left, NT * c * S, s, Xd, dinv, ts, T, c);
+    }
     launch_put_dinv(Xd, dinv, ts, NT, c, s);
   }
 }
@@ -380,47 +429,51 @@ void launch_diag_inverses(double* Xd, const double* diag, const double* dinv, in
 // second half (A_ij += P_i A_kj left of column k, row k <- X_kk A_kj, the
 // diagonal tile <- X_kk) when the two use different staging buffers.
 void launch_trtri_right(const TileMat& M, const double* Xk, double* P, int64_t k, int64_t nreal, hipStream_t s) {
-  const int64_t ts = M.ts, NT = M.NT;
-  const int T = (int)(ts / BLK);
+  const int64_t ts = M.ts, NT = M.NT, T4 = ts / BLK;
   const int64_t nbelow = NT - k - 1;
   if (nbelow <= 0) return;
+  const int B = block_tiles(nbelow * T4 * T4);
+  const int T = (int)(ts / (32 * B));
   const int64_t nr = nbelow * T * T;
-  hipLaunchKernelGGL(k_tri_right, dim3((unsigned)nr), dim3(256), 0, s, M, Xk, P, T, k, nreal, nr);
+  EXG_BLOCKS(B, k_tri_right, nr, s, M, Xk, P, T, k, nreal, nr);
   hipLaunchKernelGGL(k_copy_back, dim3((unsigned)((nbelow * ts * ts + 255) / 256)), dim3(256), 0, s, M, P, nbelow,
                      k + 1, k, 1);
 }
 
 void launch_trtri_rest(const TileMat& M, const double* Xk, double* P, int64_t k, int64_t nreal, hipStream_t s) {
-  const int64_t ts = M.ts, NT = M.NT;
-  const int T = (int)(ts / BLK);
+  const int64_t ts = M.ts, NT = M.NT, T4 = ts / BLK;
   const int64_t tt = ts * ts;
   const int64_t nbelow = NT - k - 1;
   if (nbelow > 0 && k > 0) {
+    const int B = block_tiles(nbelow * k * T4 * T4);
+    const int T = (int)(ts / (32 * B));
     const int64_t ng = nbelow * k * T * T;
-    hipLaunchKernelGGL(k_tri_gemm, dim3((unsigned)ng), dim3(256), 0, s, M, P, T, k, nreal, ng);
+    EXG_BLOCKS(B, k_tri_gemm, ng, s, M, P, T, k, nreal, ng);
   }
   if (k > 0) {
+    const int B = block_tiles(k * T4 * T4);
+    const int T = (int)(ts / (32 * B));
     const int64_t nl = k * T * T;
-    hipLaunchKernelGGL(k_tri_left, dim3((unsigned)nl), dim3(256), 0, s, M, Xk, P, T, k, nl);
+    EXG_BLOCKS(B, k_tri_left, nl, s, M, Xk, P, T, k, nl);
     hipLaunchKernelGGL(k_copy_back, dim3((unsigned)((k * tt + 255) / 256)), dim3(256), 0, s, M, P, k, k, (int64_t)0,
                        0);
   }
   launch_copy(M.diag + k * tt, Xk, tt, s);
 }
 
-int64_t lauum_blocks(int64_t ts, int64_t NT) {
-  const int64_t T = ts / BLK;
-  return NT * (NT + 1) / 2 * T * T;
-}
+int64_t lauum_blocks(int64_t ts, int64_t NT) { return NT * (NT + 1) / 2 * (ts / BLK) * (ts / BLK); }
 
-void launch_lauum_contract(const TileMat& M, int64_t nreal, const double* xs, const double* ys, const double* av,
-                           const double* qt, const double* cst, double* part, hipStream_t s) {
-  const int T = (int)(M.ts / BLK);
+// The block edge follows the number of blocks with real entries (the padded
+// ones end at once).  Returns the number of partial triples written.
+int64_t launch_lauum_contract(const TileMat& M, int64_t nreal, const double* xs, const double* ys, const double* av,
+                              const double* qt, const double* cst, double* part, hipStream_t s) {
   const int64_t t64 = M.ts / TB, npt = t64 * (t64 + 1) / 2, ntr = M.NT * (M.NT + 1) / 2 * npt;
   hipLaunchKernelGGL(k_transpose_tiles, dim3((unsigned)ntr), dim3(256), 0, s, M, npt, ntr);
-  const int64_t nb = lauum_blocks(M.ts, M.NT);
-  hipLaunchKernelGGL(k_lauum_contract, dim3((unsigned)nb), dim3(256), 0, s, M, T, nreal, xs, ys, av, qt, cst, part,
-                     nb);
+  const int64_t R = (nreal + BLK - 1) / BLK;
+  const int B = block_tiles(R * (R + 1) / 2);
+  const int64_t T = M.ts / (32 * B), nb = M.NT * (M.NT + 1) / 2 * T * T;
+  EXG_BLOCKS(B, k_lauum_contract, nb, s, M, (int)T, nreal, xs, ys, av, qt, cst, part, nb);
+  return nb;
 }
 
 }  // namespace exg

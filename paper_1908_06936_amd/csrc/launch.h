@@ -8,6 +8,22 @@
 
 namespace exg {
 
+// Edge of the output blocks of a dense product, in 32s, for a launch of nb
+// blocks of 128 x 128: 4 (128 x 128), 2 or 1.  256 CUs take the blocks in
+// rounds; a launch whose last (or only) round is nearly empty is faster on
+// smaller blocks, which read more operand bytes per flop.  Cost in units of a
+// 128 x 128 block on one CU:
+//   128: ceil(nb / 256),  64: 1.15 ceil(4 nb / 256) / 4,  32: 1.6 ceil(16 nb / 256) / 16.
+// With 128 x 128 blocks alone and with this rule: panel update and triangular
+// solve at n = 1,600 (6 - 12 blocks) 58 and 23 us a launch, 11 and 8 us;
+// trailing updates at n = 1,600 (36 blocks) 109 us, 35 us; (l, grad) at
+// n = 1,600 3,527 us, 1,823 us; DST l at n = 40,000, 4 tiles wide, 48.5 ms,
+// 26.8 ms.
+inline int block_tiles(int64_t nb) {
+  const double c4 = (double)((nb + 255) / 256), c2 = 1.15 * 0.25 * (double)((4 * nb + 255) / 256),
+               c1 = 1.6 * 0.0625 * (double)((16 * nb + 255) / 256);
+  return c4 <= c2 && c4 <= c1 ? 4 : (c2 <= c1 ? 2 : 1);
+}
 
 // k_matern.hip
 // doubles of the per-theta table array (quadrature nodes + Chebyshev tables)
@@ -115,8 +131,10 @@ void launch_diag_inverses(double* Xd, const double* diag, const double* dinv, in
 // the step's two halves: P_k and column k (any stream), then the rest
 void launch_trtri_right(const TileMat& M, const double* Xk, double* P, int64_t k, int64_t nreal, hipStream_t s);
 void launch_trtri_rest(const TileMat& M, const double* Xk, double* P, int64_t k, int64_t nreal, hipStream_t s);
-int64_t lauum_blocks(int64_t ts, int64_t NT);
-void launch_lauum_contract(const TileMat& M, int64_t nreal, const double* xs, const double* ys, const double* av,
+int64_t lauum_blocks(int64_t ts, int64_t NT);  // 128 x 128 blocks of the lower tiles
+// part: three doubles for each 32 x 32 block of the lower tiles at most;
+// returns the number of partial triples written
+int64_t launch_lauum_contract(const TileMat& M, int64_t nreal, const double* xs, const double* ys, const double* av,
                            const double* qt, const double* cst, double* part, hipStream_t s);
 
 // k_predict.hip

@@ -47,3 +47,17 @@ def test_block_factor_reports_the_first_failed_pivot(exa, pos):
     ctx = exa.Context(ts=256)
     st, ll, info = ctx.loglik_status(dev(x), dev(np.zeros(n)), dev(np.ones(n)), [4.0, 0.1, 0.5])
     assert st == exa.ENOTPD and ll == -np.inf and info == pos + 1
+
+
+# n and tile sizes at which the launches of one call take 32-, 64- and 128-wide
+# output blocks (chosen by the number of blocks), with ragged last tiles
+@pytest.mark.parametrize("n,ts", [(640, 640), (900, 384), (1300, 128), (1409, 256), (2000, 128)])
+def test_block_widths(orc, exa, n, ts):
+    ctx = exa.Context(ts=ts)
+    x, y = inputgen.uniform(n, seed=200 + n)
+    th = [0.9, 0.12, 0.7]
+    z = orc.simulate(x, y, th, inputgen.normals(n, seed=n))
+    ll_ref, g_ref = orc.loglik_grad(x, y, z, th)
+    ll, g = ctx.loglik_grad(dev(x), dev(y), dev(z), th)
+    assert ll == pytest.approx(ll_ref, rel=1e-10)
+    assert_score_close(g, g_ref, n, th)
