@@ -34,7 +34,11 @@ __device__ __forceinline__ double* low_tile(double* B, int64_t I, int64_t J, int
 
 // strip tile (jj, K) = G(J0 + jj, K) for K < NT: ts x ts, rows the points of
 // tile J0 + jj, columns those of tile K, at (jj NT + K) ts^2; zero on padding
-__global__ __launch_bounds__(256) void k_gen_dstrip(double* __restrict__ S, int comp, int T, int64_t NT, int64_t ts,
+// One kernel per parameter, so that only its own interpolation table is read
+// and evaluated (matern_grad inlines; 162 us a launch at n = 6,400 for either
+// parameter, 86 us now for beta and 123 us for nu).
+template <int COMP>
+__global__ __launch_bounds__(256) void k_gen_dstrip(double* __restrict__ S, int T, int64_t NT, int64_t ts,
                                                     int64_t J0, int64_t W, int64_t nreal,
                                                     const double* __restrict__ xs, const double* __restrict__ ys,
                                                     const double* __restrict__ qt, const double* __restrict__ cst) {
@@ -55,7 +59,7 @@ __global__ __launch_bounds__(256) void k_gen_dstrip(double* __restrict__ S, int 
     if (!ipad && gj < nreal) {
       double d0, d1, d2;
       matern_grad(loc_dist(xi, yi, xs[gj], ys[gj], cst), cst, qt, &d0, &d1, &d2);
-      val = comp == 0 ? d0 : (comp == 1 ? d1 : d2);
+      val = COMP == 0 ? d0 : (COMP == 1 ? d1 : d2);
     }
     out[(int64_t)c * ts] = val;
   }
@@ -76,13 +80,16 @@ __device__ __forceinline__ bool chunk_pair(int64_t q, int64_t NT, int64_t J0, in
   return false;
 }
 
+// Blocks of edge E = 32 B, T = ts / E per tile edge.
 // sweep 1: M(I, J) = sum_{K <= I} X(I, K) G(K, J) for the chunk's J and I >= J
 // into the lower tiles of Bm.  G(K, J)[k, n] = strip(jj, K)[n + k ts], so both
 // operands are read along their contiguous row index; X(I, I) is lower
-// triangular, so the range stops after the block's own 128 columns of tile I.
+// triangular, so the range stops after the block's own columns of tile I.
+template <int B>
 __global__ __launch_bounds__(256, 2) void k_fisher_xg(TileMat X, const double* __restrict__ S, double* __restrict__ Bm,
                                                       int T, int64_t J0, int64_t W, int64_t nreal, int64_t nb) {
-  __shared__ double sm[GEMM_LDS];
+  constexpr int E = 32 * B;
+  __shared__ double sm[gemm_lds(B, B)];
   const int64_t ts = X.ts, NT = X.NT;
   const int64_t b = blockIdx.x;
   if (b >= nb) return;
@@ -91,26 +98,28 @@ __global__ __launch_bounds__(256, 2) void k_fisher_xg(TileMat X, const double* _
   const int sub = (int)(b % (T * T));
   const int u = sub / T, v = sub % T;
   const int64_t J = J0 + jj;
-  v4d acc[4][4];
+  v4d acc[B][B];
   acc_zero(acc);
-  if (I * ts + u * BLK < nreal && J * ts + v * BLK < nreal) {
-    auto ap = [=](int k0) -> const double* { return tptr(X, I, k0 / ts) + u * BLK + (int64_t)(k0 % ts) * ts; };
+  if (I * ts + u * E < nreal && J * ts + v * E < nreal) {
+    auto ap = [=](int k0) -> const double* { return tptr(X, I, k0 / ts) + u * E + (int64_t)(k0 % ts) * ts; };
     auto bp = [=](int k0) -> const double* {
-      return S + (jj * NT + k0 / ts) * ts * ts + v * BLK + (int64_t)(k0 % ts) * ts;
+      return S + (jj * NT + k0 / ts) * ts * ts + v * E + (int64_t)(k0 % ts) * ts;
     };
-    gemm_core<false, false>(ap, ts, bp, ts, (int)(I * ts + (u + 1) * BLK), acc, sm);
+    gemm_core<false, false, false, B, B>(ap, ts, bp, ts, (int)(I * ts + (u + 1) * E), acc, sm);
   }
-  acc_store(low_tile(Bm, I, J, NT, ts) + u * BLK + (int64_t)v * BLK * ts, ts, acc, 1.0, false);
+  acc_store(low_tile(Bm, I, J, NT, ts) + u * E + (int64_t)v * E * ts, ts, acc, 1.0, false);
 }
 
 // sweep 2: B(I, J) = sum_{K <= J} M(I, K) X(J, K)^T for the chunk's J, I >= J
 // (blocks v <= u on the diagonal tile), M read from the lower tiles of Bm,
 // the result staged in stage tile (jj, I) at (jj NT + I) ts^2.  X(J, J) is
-// lower triangular: its columns beyond the block's own 128 are zero.
+// lower triangular: its columns beyond the block's own are zero.
+template <int B>
 __global__ __launch_bounds__(256, 2) void k_fisher_mxt(TileMat X, const double* __restrict__ Bm,
                                                        double* __restrict__ stage, int T, int64_t J0, int64_t W,
                                                        int64_t nreal, int64_t nb) {
-  __shared__ double sm[GEMM_LDS];
+  constexpr int E = 32 * B;
+  __shared__ double sm[gemm_lds(B, B)];
   const int64_t ts = X.ts, NT = X.NT;
   const int64_t b = blockIdx.x;
   if (b >= nb) return;
@@ -119,15 +128,18 @@ __global__ __launch_bounds__(256, 2) void k_fisher_mxt(TileMat X, const double* 
   const int sub = (int)(b % (T * T));
   const int u = sub / T, v = sub % T;
   const int64_t J = J0 + jj;
-  if ((I == J && u < v) || I * ts + u * BLK >= nreal || J * ts + v * BLK >= nreal) return;
-  v4d acc[4][4];
+  // the pass below sums whole 128 x 128 blocks: those on the diagonal and in the
+  // last real rows are formed whole
+  const int u4 = u / (4 / B), v4 = v / (4 / B);
+  if ((I == J && u4 < v4) || I * ts + u4 * BLK >= nreal || J * ts + v4 * BLK >= nreal) return;
+  v4d acc[B][B];
   acc_zero(acc);
   auto ap = [=](int k0) -> const double* {
-    return low_tile((double*)Bm, I, k0 / ts, NT, ts) + u * BLK + (int64_t)(k0 % ts) * ts;
+    return low_tile((double*)Bm, I, k0 / ts, NT, ts) + u * E + (int64_t)(k0 % ts) * ts;
   };
-  auto bp = [=](int k0) -> const double* { return tptr(X, J, k0 / ts) + v * BLK + (int64_t)(k0 % ts) * ts; };
-  gemm_core<false, false>(ap, ts, bp, ts, (int)(J * ts + (v + 1) * BLK), acc, sm);
-  acc_store(stage + (jj * NT + I) * ts * ts + u * BLK + (int64_t)v * BLK * ts, ts, acc, 1.0, false);
+  auto bp = [=](int k0) -> const double* { return tptr(X, J, k0 / ts) + v * E + (int64_t)(k0 % ts) * ts; };
+  gemm_core<false, false, false, B, B>(ap, ts, bp, ts, (int)(J * ts + (v + 1) * E), acc, sm);
+  acc_store(stage + (jj * NT + I) * ts * ts + u * E + (int64_t)v * E * ts, ts, acc, 1.0, false);
 }
 
 // lower tile (I, J0 + jj) of Bm <- stage tile (jj, I) for I >= J0 + jj; the
@@ -252,15 +264,18 @@ void launch_fisher_param(const TileMat& X, int comp, int64_t nreal, const double
     return q;
   };
   for (int64_t J0 = 0; J0 < NT; J0 += W) {
-    hipLaunchKernelGGL(k_gen_dstrip, dim3((unsigned)(W * NT * T * T)), dim3(256), 0, s, S, comp, T, NT, ts, J0, W,
-                       nreal, xs, ys, qt, cst);
-    const int64_t nb = pairs(J0) * T * T;
-    hipLaunchKernelGGL(k_fisher_xg, dim3((unsigned)nb), dim3(256), 0, s, X, (const double*)S, Bm, T, J0, W, nreal, nb);
+    hipLaunchKernelGGL(comp == 0 ? k_gen_dstrip<0> : (comp == 1 ? k_gen_dstrip<1> : k_gen_dstrip<2>),
+                       dim3((unsigned)(W * NT * T * T)), dim3(256), 0, s, S, T, NT, ts, J0, W, nreal, xs, ys, qt, cst);
+    const int B = block_tiles_uneven(pairs(J0) * T * T);
+    const int Tb = (int)(ts / (32 * B));
+    const int64_t nb = pairs(J0) * Tb * Tb;
+    EXG_BLOCKS(B, k_fisher_xg, nb, s, X, (const double*)S, Bm, Tb, J0, W, nreal, nb);
   }
   for (int64_t J0 = (NT - 1) / W * W; J0 >= 0; J0 -= W) {
-    const int64_t nb = pairs(J0) * T * T;
-    hipLaunchKernelGGL(k_fisher_mxt, dim3((unsigned)nb), dim3(256), 0, s, X, (const double*)Bm, S, T, J0, W, nreal,
-                       nb);
+    const int B = block_tiles_uneven(pairs(J0) * T * T);
+    const int Tb = (int)(ts / (32 * B));
+    const int64_t nb = pairs(J0) * Tb * Tb;
+    EXG_BLOCKS(B, k_fisher_mxt, nb, s, X, (const double*)Bm, S, Tb, J0, W, nreal, nb);
     hipLaunchKernelGGL(k_fisher_unstage, dim3((unsigned)((W * NT * tt + 255) / 256)), dim3(256), 0, s,
                        (const double*)S, Bm, NT, ts, J0, W);
   }

@@ -333,16 +333,6 @@ __global__ __launch_bounds__(256, 2) void k_lauum_contract(TileMat M, int T, int
 }
 
 // ------------------------------------------------------------- launchers
-#define EXG_BLOCKS(tiles, kernel, grid, stream, ...)                                                     \
-  do {                                                                                                   \
-    if ((tiles) == 4)                                                                                    \
-      hipLaunchKernelGGL(kernel<4>, dim3((unsigned)(grid)), dim3(256), 0, stream, __VA_ARGS__);          \
-    else if ((tiles) == 2)                                                                               \
-      hipLaunchKernelGGL(kernel<2>, dim3((unsigned)(grid)), dim3(256), 0, stream, __VA_ARGS__);          \
-    else                                                                                                 \
-      hipLaunchKernelGGL(kernel<1>, dim3((unsigned)(grid)), dim3(256), 0, stream, __VA_ARGS__);          \
-  } while (0)
-
 static void update_pairs(const TileMat& M, const double* below, int64_t k, int64_t nreal, int mode, int64_t off,
                          int64_t npairs, const int32_t* li, const int32_t* lj, hipStream_t s) {
   const int64_t T4 = M.ts / BLK;
@@ -470,7 +460,7 @@ int64_t launch_lauum_contract(const TileMat& M, int64_t nreal, const double* xs,
   const int64_t t64 = M.ts / TB, npt = t64 * (t64 + 1) / 2, ntr = M.NT * (M.NT + 1) / 2 * npt;
   hipLaunchKernelGGL(k_transpose_tiles, dim3((unsigned)ntr), dim3(256), 0, s, M, npt, ntr);
   const int64_t R = (nreal + BLK - 1) / BLK;
-  const int B = block_tiles(R * (R + 1) / 2);
+  const int B = block_tiles_uneven(R * (R + 1) / 2);
   const int64_t T = M.ts / (32 * B), nb = M.NT * (M.NT + 1) / 2 * T * T;
   EXG_BLOCKS(B, k_lauum_contract, nb, s, M, (int)T, nreal, xs, ys, av, qt, cst, part, nb);
   return nb;

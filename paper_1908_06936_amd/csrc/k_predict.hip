@@ -50,37 +50,41 @@ __global__ __launch_bounds__(256) void k_gen_cross(const double* __restrict__ xs
   C[j + c * ldc] = v;
 }
 
-// V_k = X_kk C_k on the 128-row blocks u of tile row k, columns in 128-wide
-// blocks cb; X_kk lower triangular, so the k range stops at (u + 1) 128.
+// V_k = X_kk C_k on (32 B) x (32 B) blocks (u, cb), T = ts / (32 B) block rows;
+// X_kk lower triangular, so the k range stops at the block's own rows.
+template <int B>
 __global__ __launch_bounds__(256, 2) void k_trsm_diag(const double* __restrict__ Xk, int64_t ts,
                                                       const double* __restrict__ Ck, double* __restrict__ Vk,
                                                       int64_t ld, int T) {
-  __shared__ double sm[GEMM_LDS];
-  const int u = (int)(blockIdx.x % T);
+  constexpr int E = 32 * B;
+  __shared__ double sm[gemm_lds(B, B)];
+  const int u = T - 1 - (int)(blockIdx.x % T);  // longest k range first
   const int64_t cb = blockIdx.x / T;
-  v4d acc[4][4];
+  v4d acc[B][B];
   acc_zero(acc);
-  // Aop(m, q) = X[u*128 + m, q], Bop(n, q) = C[q, cb*128 + n]
-  gemm_blk<false, true, true>(Xk + u * BLK, ts, Ck + cb * BLK * ld, ld, (u + 1) * BLK, acc, sm);
-  acc_store(Vk + u * BLK + cb * BLK * ld, ld, acc, 1.0, false);
+  // Aop(m, q) = X[u E + m, q], Bop(n, q) = C[q, cb E + n]
+  gemm_blk<false, true, true, B, B>(Xk + u * E, ts, Ck + cb * E * ld, ld, (u + 1) * E, acc, sm);
+  acc_store(Vk + u * E + cb * E * ld, ld, acc, 1.0, false);
 }
 
-// C_i -= L_ik V_k for the tiles i > k with real rows, 128 x 128 blocks
-// (i, u, cb); g0 = first global 128-row block below tile k.
+// C_i -= L_ik V_k for the tiles i > k with real rows, (32 B) x (32 B) blocks
+// (g, cb); g0 = first block row below tile k, nrb block rows.
+template <int B>
 __global__ __launch_bounds__(256, 2) void k_trsm_update(TileMat M, int64_t k, int64_t g0,
                                                         const double* __restrict__ Vk, double* __restrict__ C,
                                                         int64_t ld, int T, int64_t nrb) {
-  __shared__ double sm[GEMM_LDS];
+  constexpr int E = 32 * B;
+  __shared__ double sm[gemm_lds(B, B)];
   const int64_t ts = M.ts;
   const int64_t g = g0 + blockIdx.x % nrb;
   const int64_t cb = blockIdx.x / nrb;
   const int64_t i = g / T;
   const int u = (int)(g % T);
-  v4d acc[4][4];
+  v4d acc[B][B];
   acc_zero(acc);
-  // Aop(m, q) = L_ik[u*128 + m, q], Bop(n, q) = V_k[q, cb*128 + n]
-  gemm_blk<false, true, true>(tptr(M, i, k) + u * BLK, ts, Vk + cb * BLK * ld, ld, (int)ts, acc, sm);
-  acc_store(C + i * ts + u * BLK + cb * BLK * ld, ld, acc, -1.0, true);
+  // Aop(m, q) = L_ik[u E + m, q], Bop(n, q) = V_k[q, cb E + n]
+  gemm_blk<false, true, true, B, B>(tptr(M, i, k) + u * E, ts, Vk + cb * E * ld, ld, (int)ts, acc, sm);
+  acc_store(C + i * ts + u * E + cb * E * ld, ld, acc, -1.0, true);
 }
 
 // mse[c0 + c] = sigma^2 - sum_j V[j, c]^2, one workgroup per column
@@ -111,19 +115,21 @@ void launch_krige_mse(const TileMat& M, const double* Xd, const double* xs, cons
                       const double* xn, const double* yn, int64_t m, int64_t c0, int64_t ncols, const double* qt,
                       const double* cst, double* C, double* V, double* mse, hipStream_t s) {
   const int64_t ts = M.ts, NT = M.NT, npad = NT * ts, ld = npad;
-  const int T = (int)(ts / BLK);
-  const int64_t ncb = ncols / BLK;  // ncols is a multiple of 128
+  const int64_t T4 = ts / BLK, ncb = ncols / BLK;  // ncols is a multiple of 128
   hipLaunchKernelGGL(k_gen_cross, dim3((unsigned)((npad + 255) / 256), (unsigned)ncols), dim3(256), 0, s, xs, ys,
                      nreal, npad, xn, yn, m, c0, ncols, qt, cst, C, ld);
   const int64_t gmax = (nreal + BLK - 1) / BLK;  // 128-row blocks holding real rows
   for (int64_t k = 0; k < NT; ++k) {
-    hipLaunchKernelGGL(k_trsm_diag, dim3((unsigned)(T * ncb)), dim3(256), 0, s, Xd + k * ts * ts, ts, C + k * ts,
-                       V + k * ts, ld, T);
-    const int64_t g0 = (k + 1) * T;
+    {
+      const int B = block_tiles(T4 * ncb), S = 4 / B;
+      EXG_BLOCKS(B, k_trsm_diag, T4 * S * ncb * S, s, Xd + k * ts * ts, ts, C + k * ts, V + k * ts, ld, (int)T4 * S);
+    }
+    const int64_t g0 = (k + 1) * T4;
     if (gmax > g0) {
       const int64_t nrb = gmax - g0;
-      hipLaunchKernelGGL(k_trsm_update, dim3((unsigned)(nrb * ncb)), dim3(256), 0, s, M, k, g0,
-                         (const double*)(V + k * ts), C, ld, T, nrb);
+      const int B = block_tiles(nrb * ncb), S = 4 / B;
+      EXG_BLOCKS(B, k_trsm_update, nrb * S * ncb * S, s, M, k, g0 * S, (const double*)(V + k * ts), C, ld,
+                 (int)T4 * S, nrb * S);
     }
   }
   hipLaunchKernelGGL(k_col_mse, dim3((unsigned)ncols), dim3(256), 0, s, (const double*)V, ld, npad, m, c0, cst, mse);

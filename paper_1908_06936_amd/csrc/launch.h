@@ -25,6 +25,23 @@ inline int block_tiles(int64_t nb) {
   return c4 <= c2 && c4 <= c1 ? 4 : (c2 <= c1 ? 2 : 1);
 }
 
+// The same where the k range differs from block to block (the longest ones
+// decide): 128 x 128 only where several rounds even it out.  Fisher products
+// at n = 6,400 (about 400 blocks a launch): xg 1,159 us on 128 x 128, 656 us
+// on 64 x 64 blocks.
+inline int block_tiles_uneven(int64_t nb) { return nb >= 1536 ? 4 : (nb >= 64 ? 2 : 1); }
+
+// kernel<B> for the block edge 32 B, 256 threads per workgroup
+#define EXG_BLOCKS(tiles, kernel, grid, stream, ...)                                                     \
+  do {                                                                                                   \
+    if ((tiles) == 4)                                                                                    \
+      hipLaunchKernelGGL(kernel<4>, dim3((unsigned)(grid)), dim3(256), 0, stream, __VA_ARGS__);          \
+    else if ((tiles) == 2)                                                                               \
+      hipLaunchKernelGGL(kernel<2>, dim3((unsigned)(grid)), dim3(256), 0, stream, __VA_ARGS__);          \
+    else                                                                                                 \
+      hipLaunchKernelGGL(kernel<1>, dim3((unsigned)(grid)), dim3(256), 0, stream, __VA_ARGS__);          \
+  } while (0)
+
 // k_matern.hip
 // doubles of the per-theta table array (quadrature nodes + Chebyshev tables)
 int64_t quad_table_doubles();

@@ -61,3 +61,30 @@ def test_block_widths(orc, exa, n, ts):
     ll, g = ctx.loglik_grad(dev(x), dev(y), dev(z), th)
     assert ll == pytest.approx(ll_ref, rel=1e-10)
     assert_score_close(g, g_ref, n, th)
+
+
+# kriging and the Fisher information on the narrow blocks: few and many new
+# points (blocks of 128 columns, ragged), one tile and several, padded last rows
+@pytest.mark.parametrize("n,ts,m", [(130, 128, 1), (300, 512, 130), (900, 256, 700), (1100, 128, 1500)])
+def test_kriging_block_widths(orc, exa, n, ts, m):
+    ctx = exa.Context(ts=ts)
+    x, y = inputgen.uniform(n, seed=300 + n)
+    xn, yn = inputgen.uniform(m, seed=400 + m)
+    th = [1.1, 0.1, 0.8]
+    z = orc.simulate(x, y, th, inputgen.normals(n, seed=n))
+    mean, mse = ctx.predict(dev(x), dev(y), dev(z), th, dev(xn), dev(yn))
+    mean_ref, mse_ref = orc.predict(x, y, z, th, xn, yn)
+    np.testing.assert_allclose(mean.cpu().numpy(), mean_ref, rtol=0, atol=1e-9 * np.abs(mean_ref).max())
+    np.testing.assert_allclose(mse.cpu().numpy(), mse_ref, rtol=0, atol=1e-9 * th[0])
+
+
+@pytest.mark.parametrize("n,ts,nugget", [(129, 128, 0.0), (400, 512, 0.0), (700, 128, 0.1), (900, 384, 0.0)])
+def test_fisher_block_widths(orc, exa, n, ts, nugget):
+    ctx = exa.Context(ts=ts)
+    ctx.set_nugget(nugget)
+    x, y = inputgen.uniform(n, seed=500 + n)
+    th = [1.3, 0.1, 0.6]
+    ref = orc.fisher(x, y, th, nugget)
+    got = ctx.fisher(dev(x), dev(y), th)
+    d = np.sqrt(np.diag(ref))
+    assert np.max(np.abs(got - ref) / np.outer(d, d)) <= 1e-9
