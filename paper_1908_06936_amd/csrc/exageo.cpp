@@ -181,6 +181,10 @@ struct exageo_ctx {
   // side stream (default priority) for the lookahead panel, and its events
   hipStream_t side = nullptr;
   hipEvent_t ev_col = nullptr, ev_panel = nullptr;
+  // stream (default priority) of the forward solve beside the factorisation,
+  // made by the first call with more than one tile
+  hipStream_t fwd = nullptr;
+  hipEvent_t ev_fwd = nullptr;
   // profiling
   hipEvent_t ev[NEV];
   int nev_created = 0;
@@ -276,8 +280,8 @@ constexpr int EV_UPD0 = 8;
 
 exageo_status prepare_locations(exageo_ctx* c, const Plan& p, const double* x, const double* y, const double* z) {
   exg::launch_sort_locations(x, y, z, p.n, p.npad, p.P, at<double>(c, p.off_box), at<uint64_t>(c, p.off_keys),
-                             at<double>(c, p.off_xs), at<double>(c, p.off_ys), at<double>(c, p.off_zs),
-                             at<int32_t>(c, p.off_perm), c->stream);
+                             at<int32_t>(c, p.off_tmp), at<double>(c, p.off_xs), at<double>(c, p.off_ys),
+                             at<double>(c, p.off_zs), at<int32_t>(c, p.off_perm), c->stream);
   HIPCHK(c, hipGetLastError());
   if (p.mixed) {
     // bounding boxes of the location blocks of the tiles, for the precision map
@@ -461,8 +465,10 @@ double* below_fp64(const exg::TileMat& M, int64_t k) {
   return (double*)M.off + exg::off_index(k + 1, k, M.NT) * M.ts * M.ts;
 }
 
-// Sigma(theta) tiles and their Cholesky factor in place.
-exageo_status factorize(exageo_ctx* c, const Plan& p, const double theta[3]) {
+// Sigma(theta) tiles and their Cholesky factor in place.  solve: also y =
+// L^-1 z tile by tile on a stream of its own, tile k as soon as panel k is
+// factored; the last tile is left to solve_reduce.
+exageo_status factorize(exageo_ctx* c, const Plan& p, const double theta[3], bool solve) {
   const exg::TileMat M = tilemat(c, p);
   const int64_t tt = p.ts * p.ts;
   const uint8_t* tag = nullptr;
@@ -470,7 +476,8 @@ exageo_status factorize(exageo_ctx* c, const Plan& p, const double theta[3]) {
   c->timings[11] = 0.0;
   c->timings[12] = 0.0;
   c->timings[14] = 0.0;
-  exg::launch_quad_table(theta, c->metric, c->nugget, at<double>(c, p.off_qt), at<double>(c, p.off_cst), c->stream);
+  exg::launch_quad_table(theta, c->metric, c->nugget, at<double>(c, p.off_qt), at<double>(c, p.off_cst),
+                         at<unsigned long long>(c, p.off_info), c->stream);
   if (p.mixed) {
     double fbf = 0.0, f64 = 0.0;
     exageo_status st = upload_tags(c, p, theta, &fbf, &f64);
@@ -480,9 +487,9 @@ exageo_status factorize(exageo_ctx* c, const Plan& p, const double theta[3]) {
     c->timings[12] = p.NT > 1 ? 1.0 - fbf - f64 : 0.0;
     c->timings[14] = f64;
   }
-  exg::launch_fill_info(at<unsigned long long>(c, p.off_info), c->stream);
+  // DST: the tiles outside the band are read only once the inverse fills them
   exg::launch_gen_tiles(M, p.n, at<double>(c, p.off_xs), at<double>(c, p.off_ys), at<double>(c, p.off_qt),
-                        at<double>(c, p.off_cst), tag, c->stream);
+                        at<double>(c, p.off_cst), tag, p.grad, c->stream);
   rec(c, 2);
   double upd_flops = 0.0;
   double flops_by[3] = {0.0, 0.0, 0.0};  // FP32, BF16, FP64 targets
@@ -521,8 +528,24 @@ exageo_status factorize(exageo_ctx* c, const Plan& p, const double theta[3]) {
     }
     return below;
   };
+  double* rhs = at<double>(c, p.off_yv);
+  double* yv = at<double>(c, p.off_y);
+  const double* dinv = at<double>(c, p.off_dinv);
+  if (solve && p.NT > 1 && !c->ev_fwd) {
+    if (!c->fwd) HIPCHK(c, hipStreamCreateWithFlags(&c->fwd, hipStreamNonBlocking));
+    HIPCHK(c, hipEventCreateWithFlags(&c->ev_fwd, hipEventDisableTiming));
+  }
+  hipStream_t S3 = c->fwd;
+  if (solve) exg::launch_copy(rhs, at<double>(c, p.off_zs), p.npad, S);
   double* below = panel(0, S);
+  if (solve && p.NT > 1) HIPCHK(c, hipEventRecord(c->ev_panel, S));
   for (int64_t k = 0; k + 1 < p.NT; ++k) {
+    if (solve) {
+      HIPCHK(c, hipStreamWaitEvent(S3, c->ev_panel, 0));  // panel k
+      exg::launch_solve_tile(M, k, dinv + k * p.T * BLKH * BLKH, p.n, rhs, yv, S3);
+      if (p.mixed) exg::launch_solve_below_lp(M, tag, k, p.n, yv, rhs, S3);
+      else exg::launch_solve_below(M, k, p.n, yv, rhs, S3);
+    }
     float* p32 = p.mixed ? at<float>(c, p.off_p32) + (k & 1) * phalf : nullptr;
     const uint16_t* pbt = p.mixed && any_bf16 ? at<uint16_t>(c, p.off_pbt) + (k & 1) * phalf : nullptr;
     const int slot = EV_UPD0 + 2 * (int)k;
@@ -573,6 +596,10 @@ exageo_status factorize(exageo_ctx* c, const Plan& p, const double theta[3]) {
       }
     }
   }
+  if (solve && p.NT > 1) {
+    HIPCHK(c, hipEventRecord(c->ev_fwd, S3));
+    HIPCHK(c, hipStreamWaitEvent(S, c->ev_fwd, 0));
+  }
   HIPCHK(c, hipGetLastError());
   rec(c, 3);
   c->timings[5] = upd_flops;
@@ -584,8 +611,15 @@ exageo_status factorize(exageo_ctx* c, const Plan& p, const double theta[3]) {
   return EXAGEO_OK;
 }
 
-// y = L^-1 z with the explicit inverses of the diagonal tiles, then eq. (2).
-// Mixed precision with refinement steps: a = Sigma^-1 z through the mixed
+// the explicit inverses X_kk of the diagonal tiles of L
+double* diag_inverses(exageo_ctx* c, const Plan& p) {
+  double* Xd = at<double>(c, p.off_xd);
+  exg::launch_diag_inverses(Xd, at<double>(c, p.off_diag), at<double>(c, p.off_dinv), p.ts, p.NT, c->stream);
+  return Xd;
+}
+
+// The last tile of y = L^-1 z, after the others beside the factorisation, then
+// eq. (2).  Mixed precision with refinement steps: a = Sigma^-1 z through the mixed
 // factor (forward and backward solves) and its residual r = z - Sigma a with
 // Sigma regenerated in FP64; each step tries a + (mixed factor)^-1 r and keeps
 // it only if its residual is smaller (a step that does not contract, as when
@@ -596,13 +630,14 @@ exageo_status solve_reduce(exageo_ctx* c, const Plan& p) {
   double* rhs = at<double>(c, p.off_yv);
   double* y = at<double>(c, p.off_y);
   const exg::TileMat M = tilemat(c, p);
-  double* Xd = at<double>(c, p.off_xd);
-  exg::launch_diag_inverses(Xd, M.diag, at<double>(c, p.off_dinv), p.ts, p.NT, c->stream);
-  exg::launch_copy(rhs, at<double>(c, p.off_zs), p.npad, c->stream);
+  const unsigned long long* info = at<unsigned long long>(c, p.off_info);
+  const double* box = at<double>(c, p.off_box);
+  const int64_t last = p.NT - 1;
+  exg::launch_solve_tile(M, last, at<double>(c, p.off_dinv) + last * p.T * BLKH * BLKH, p.n, rhs, y, c->stream);
   c->timings[21] = 0.0;
   if (p.mixed) {
     const uint8_t* tag = at<uint8_t>(c, p.off_tag);
-    exg::launch_trsv_fwd_lp(M, tag, Xd, p.n, rhs, y, c->stream);
+    const double* Xd = c->refine > 0 || p.grad ? diag_inverses(c, p) : nullptr;
     if (c->refine > 0) {
       double* av = at<double>(c, p.off_alpha);  // accepted a
       double* at_ = at<double>(c, p.off_y);      // trial a (y is not needed any more)
@@ -627,17 +662,16 @@ exageo_status solve_reduce(exageo_ctx* c, const Plan& p) {
         exg::launch_resid_norm(rt, p.npad, nrm, 1, c->stream);
         exg::launch_refine_select(av, at_, r, rt, nrm, p.npad, c->stream);
       }
-      exg::launch_finalize_loglik_za(zs, av, p.n, at<double>(c, p.off_ld), p.NT * p.T, at<double>(c, p.off_out),
-                                     c->stream);
+      exg::launch_finalize_loglik_za(zs, av, p.n, at<double>(c, p.off_ld), p.NT * p.T, info, box,
+                                     at<double>(c, p.off_out), c->stream);
       c->timings[21] = c->refine;
       HIPCHK(c, hipGetLastError());
       rec(c, 4);
       return EXAGEO_OK;
     }
-  } else {
-    exg::launch_trsv_fwd(M, Xd, p.n, rhs, y, c->stream);
   }
-  exg::launch_finalize_loglik(y, p.n, at<double>(c, p.off_ld), p.NT * p.T, at<double>(c, p.off_out), c->stream);
+  exg::launch_finalize_loglik(y, p.n, at<double>(c, p.off_ld), p.NT * p.T, info, box, at<double>(c, p.off_out),
+                              c->stream);
   HIPCHK(c, hipGetLastError());
   rec(c, 4);
   return EXAGEO_OK;
@@ -671,7 +705,7 @@ exageo_status gradient(exageo_ctx* c, const Plan& p) {
   const exg::TileMat M = tilemat(c, p);
   double* rhs = at<double>(c, p.off_av);
   double* av = at<double>(c, p.off_alpha);
-  double* Xd = at<double>(c, p.off_xd);
+  double* Xd = p.mixed ? at<double>(c, p.off_xd) : diag_inverses(c, p);  // mixed: formed for the solve
   int64_t nparts = 0;  // partial triples of the contraction
   double* part = at<double>(c, p.off_part);
   const int64_t tt = p.ts * p.ts, half = std::max<int64_t>(1, p.NT - 1) * tt;
@@ -724,17 +758,15 @@ exageo_status gradient(exageo_ctx* c, const Plan& p) {
   return EXAGEO_OK;
 }
 
-// copy out[0..5] and info to the host and wait
+// copy the results, the failed pivot and the box to the host and wait
 exageo_status fetch(exageo_ctx* c, const Plan& p, double* out6, int64_t* info_sorted, double* box_flag) {
-  HIPCHK(c, hipMemcpyAsync(c->hres, at<double>(c, p.off_out), 6 * 8, hipMemcpyDeviceToHost, c->stream));
-  HIPCHK(c, hipMemcpyAsync(c->hres + 6, at<double>(c, p.off_info), 8, hipMemcpyDeviceToHost, c->stream));
-  HIPCHK(c, hipMemcpyAsync(c->hres + 7, at<double>(c, p.off_box), 5 * 8, hipMemcpyDeviceToHost, c->stream));
+  HIPCHK(c, hipMemcpyAsync(c->hres, at<double>(c, p.off_out), exg::OUT_COUNT * 8, hipMemcpyDeviceToHost, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
   memcpy(out6, c->hres, 6 * 8);
   uint64_t inf;
-  memcpy(&inf, c->hres + 6, 8);
+  memcpy(&inf, c->hres + exg::OUT_INFO, 8);
   *info_sorted = (inf == ~(uint64_t)0) ? 0 : (int64_t)inf;
-  if (box_flag) memcpy(box_flag, c->hres + 7, 5 * 8);
+  if (box_flag) memcpy(box_flag, c->hres + exg::OUT_BOX, 5 * 8);
   return EXAGEO_OK;
 }
 
@@ -810,6 +842,11 @@ void exageo_destroy(exageo_ctx* c) {
     (void)hipStreamSynchronize(c->side);
     (void)hipStreamDestroy(c->side);
   }
+  if (c->fwd) {
+    (void)hipStreamSynchronize(c->fwd);
+    (void)hipStreamDestroy(c->fwd);
+  }
+  if (c->ev_fwd) (void)hipEventDestroy(c->ev_fwd);
   if (c->ev_col) (void)hipEventDestroy(c->ev_col);
   if (c->ev_panel) (void)hipEventDestroy(c->ev_panel);
   delete c;
@@ -932,7 +969,8 @@ exageo_status exageo_matern_cov(exageo_ctx* c, int64_t n, const double* x, const
   Plan p = make_plan(1, c->ts, 0);
   exageo_status st = ensure_ws(c, p);
   if (st) return st;
-  exg::launch_quad_table(theta, c->metric, c->nugget, at<double>(c, p.off_qt), at<double>(c, p.off_cst), c->stream);
+  exg::launch_quad_table(theta, c->metric, c->nugget, at<double>(c, p.off_qt), at<double>(c, p.off_cst), nullptr,
+                         c->stream);
   exg::launch_gen_dense(cov, ldc, n, x, y, at<double>(c, p.off_qt), at<double>(c, p.off_cst), c->stream);
   HIPCHK(c, hipGetLastError());
   HIPCHK(c, hipStreamSynchronize(c->stream));
@@ -942,7 +980,7 @@ exageo_status exageo_matern_cov(exageo_ctx* c, int64_t n, const double* x, const
 // evaluation at theta on locations already sorted into the workspace
 static exageo_status eval_sorted(exageo_ctx* c, const Plan& p, const double theta[3], bool want_grad, double* loglik,
                                  double* grad, int64_t* info, bool check_box) {
-  exageo_status st = factorize(c, p, theta);
+  exageo_status st = factorize(c, p, theta, true);
   if (st) return st;
   st = solve_reduce(c, p);
   if (st) return st;
@@ -1063,7 +1101,7 @@ exageo_status exageo_simulate(exageo_ctx* c, int64_t n, const double* x, const d
   // sorted copy of e goes to zs
   st = prepare_locations(c, p, x, y, e);
   if (st) return st;
-  st = factorize(c, p, theta);
+  st = factorize(c, p, theta, false);
   if (st) return st;
   double* w = at<double>(c, p.off_tmp);
   exg::launch_trmv_lower(tilemat(c, p), p.n, at<double>(c, p.off_zs), w, c->stream);
@@ -1071,7 +1109,8 @@ exageo_status exageo_simulate(exageo_ctx* c, int64_t n, const double* x, const d
   HIPCHK(c, hipGetLastError());
   double out[6], box[5];
   int64_t inf = 0;
-  exg::launch_finalize_loglik(w, p.n, at<double>(c, p.off_ld), p.NT * p.T, at<double>(c, p.off_out), c->stream);
+  exg::launch_finalize_loglik(w, p.n, at<double>(c, p.off_ld), p.NT * p.T, at<unsigned long long>(c, p.off_info),
+                              at<double>(c, p.off_box), at<double>(c, p.off_out), c->stream);
   st = fetch(c, p, out, &inf, box);
   if (st) return st;
   if (!inputs_finite(box)) return fail(c, EXAGEO_EINVAL, "non-finite location or draw");
@@ -1216,7 +1255,7 @@ exageo_status exageo_predict(exageo_ctx* c, int64_t n, const double* x, const do
   if (st) return st;
   if (m == 0) return EXAGEO_OK;
   const exg::TileMat M = tilemat(c, p);
-  double* Xd = at<double>(c, p.off_xd);
+  double* Xd = diag_inverses(c, p);
   double* av = at<double>(c, p.off_alpha);
   // a = Sigma^-1 z = L^-T y, then the mean in one pass over (new, observed) pairs
   exg::launch_copy(at<double>(c, p.off_av), at<double>(c, p.off_y), p.npad, c->stream);
@@ -1265,7 +1304,7 @@ exageo_status exageo_fisher(exageo_ctx* c, int64_t n, const double* x, const dou
   st = eval_sorted(c, p, theta, false, &ll, nullptr, info, true);
   if (st) return st;
   const exg::TileMat M = tilemat(c, p);
-  double* Xd = at<double>(c, p.off_xd);
+  double* Xd = diag_inverses(c, p);
   // L^-1 in place (the tile matrix then holds X = L^-1, lower-triangular tiles)
   {
     const int64_t tt = p.ts * p.ts, half = std::max<int64_t>(1, p.NT - 1) * tt;

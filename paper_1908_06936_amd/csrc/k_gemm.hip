@@ -377,7 +377,11 @@ void launch_panel(double* Dk, double* below, int64_t ts, int64_t NT, int64_t k, 
   (void)NT;
   for (int c = 0; c < T; ++c) {
     const int64_t gd = k * T + c;  // global index of the diagonal block
-    if (c > 0 && gmax > gd) {
+    if (gd >= gmax) {  // the rest of the tile is padding, the identity
+      launch_pad_blocks(dinv_k + (int64_t)c * BLK * BLK, ldpart_k + c, T - c, s);
+      break;
+    }
+    if (c > 0) {
       const int B = block_tiles(gmax - gd);
       EXG_BLOCKS(B, k_panel_update, (gmax - gd) * (4 / B) * (4 / B), s, Dk, below, ts, T, k, c, gd);
     }

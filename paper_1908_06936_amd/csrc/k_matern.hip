@@ -23,8 +23,9 @@ __device__ double dev_digamma(double z) {
 
 // One thread per (bucket m, node k): node t = k h_m, weights of the three
 // integrands including the trapezoidal end weight h/2 at t = 0.
+// info (may be null): the first failed pivot, reset for the factorisation.
 __global__ void k_quad_table(double s2, double beta, double nu, double metric, double nugget,
-                             double* __restrict__ qt, double* __restrict__ cst) {
+                             double* __restrict__ qt, double* __restrict__ cst, unsigned long long* info) {
   const int m = blockIdx.x, k = threadIdx.x;
   const double h = 0.1 * exp2(-0.5 * m);
   const double t = k * h;
@@ -46,6 +47,7 @@ __global__ void k_quad_table(double s2, double beta, double nu, double metric, d
     cst[C_S2C] = s2 * c;
     cst[C_METRIC] = metric;
     cst[C_NUG] = nugget;
+    if (info) *info = ~0ull;
   }
 }
 
@@ -54,28 +56,50 @@ __global__ void k_quad_table(double s2, double beta, double nu, double metric, d
 // are its value at the segment centre (the middle point, t = 0) and the
 // Chebyshev coefficients of ln(u / u_centre), c_k = (2/N) sum_j d_j
 // cos(pi k (j + 1/2) / N), whose magnitudes stay small.  Runs after
-// k_quad_table.
-__global__ __launch_bounds__(64) void k_cheb_table(double* __restrict__ qt, const double* __restrict__ cst) {
-  __shared__ double fv[3][CH_N];
-  const int seg = blockIdx.x, j = threadIdx.x;
+// k_quad_table.  Bound by latency: 16 lanes share the up to 400 nodes of one
+// point and the logarithms and cosines are formed once, one per thread
+// (68 us with a thread per point and per coefficient, 12 us so).
+__global__ __launch_bounds__(256) void k_cheb_table(double* __restrict__ qt, const double* __restrict__ cst) {
+  constexpr int LP = 16;  // lanes per point
+  __shared__ double fv[3][CH_N], lg[3][CH_N], cs[CH_N][CH_N];
+  const int seg = blockIdx.x, t = threadIdx.x;
+  const double pi = 3.14159265358979323846;
   const double nu = cst[C_NU];
-  if (j < CH_N) {
-    const double tj = cos(3.14159265358979323846 * (j + 0.5) / CH_N);
+  if (t < CH_N * CH_N) cs[t / CH_N][t % CH_N] = cos(pi * (t / CH_N) * (t % CH_N + 0.5) / CH_N);
+  if (t < CH_N * LP) {
+    const int j = t / LP, l = t % LP;
+    const double tj = cos(pi * (j + 0.5) / CH_N);
     const double x = exp(CH_SLO + (seg + 0.5 * (tj + 1.0)) * CH_DS);
-    double t0, t1, t2;
-    quad_k3(qt, x, nu, &t0, &t1, &t2);
-    const double xn = pow(x, nu);
-    fv[0][j] = xn * t0;
-    fv[1][j] = xn * x * t1;
-    fv[2][j] = xn * t2;
+    const double* q = qt + (quad_bucket(x) * QNK + l) * QW;
+    double a = 0.0, b = 0.0, c2 = 0.0;
+    for (int k = l; k < QNK; k += LP, q += LP * QW) {
+      const double c = q[0];
+      if (k > 0 && x * c - nu * q[1] > QCUT + 5.0) break;
+      const double e = exp(-x * c);
+      a += e * q[2];
+      b += e * q[3];
+      c2 += e * q[4];
+    }
+    for (int o = LP / 2; o > 0; o >>= 1) {
+      a += __shfl_xor(a, o, LP);
+      b += __shfl_xor(b, o, LP);
+      c2 += __shfl_xor(c2, o, LP);
+    }
+    if (l == 0) {
+      const double xn = pow(x, nu);
+      fv[0][j] = xn * a;
+      fv[1][j] = xn * x * b;
+      fv[2][j] = xn * c2;
+    }
   }
   __syncthreads();
-  if (j < 3 * 16) {
-    const int f = j >> 4, k = j & 15;
+  if (t < 3 * CH_N) lg[t / CH_N][t % CH_N] = log(fv[t / CH_N][t % CH_N] / fv[t / CH_N][CH_MID]);
+  __syncthreads();
+  if (t < 3 * 16) {
+    const int f = t >> 4, k = t & 15;
     double c = 0.0;
     if (k < CH_N) {
-      for (int q = 0; q < CH_N; ++q)
-        c += log(fv[f][q] / fv[f][CH_MID]) * cos(3.14159265358979323846 * k * (q + 0.5) / CH_N);
+      for (int q = 0; q < CH_N; ++q) c += lg[f][q] * cs[k][q];
       c *= 2.0 / CH_N;
     } else if (k == CH_N) {
       c = fv[f][CH_MID];
@@ -96,20 +120,26 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
 // are not needed by any later step and are skipped.  Mixed precision (tag !=
 // NULL): diagonal tiles FP64, off-diagonal tiles FP32 (tag 0) or BF16 (tag 1),
 // each rounded to nearest even from the FP64 value, or FP64 in the band pool
-// (tag 2).
+// (tag 2).  A block's columns are shared by `parts` workgroups: 1 where the
+// blocks fill the chip, 8 where they would not (n = 400, 16 real blocks: 73 us
+// with 64 entries one after another in each thread, 14 us with 8).  Tiles
+// outside the DST band are zero and are written only if fill_zero.
 __global__ __launch_bounds__(256) void k_gen_tiles(TileMat M, int T, int64_t nreal, const double* __restrict__ xs,
                                                    const double* __restrict__ ys, const double* __restrict__ qt,
                                                    const double* __restrict__ cst, const uint8_t* __restrict__ tag,
-                                                   int64_t tile_first) {
+                                                   int64_t tile_first, int parts, int fill_zero) {
   const int64_t ts = M.ts;
-  const int64_t b = blockIdx.x;
+  const int64_t b = blockIdx.x / parts;
+  const int part = blockIdx.x % parts, ncol = BLK / parts;
   const int64_t p = tile_first + b / (T * T);
   const int sub = (int)(b % (T * T));
   const int u = sub / T, v = sub % T;
   int64_t I, J;
   tri_decode(p, &I, &J);
   if (I == J && u < v) return;
-  const int r = threadIdx.x & 127, c0 = threadIdx.x >> 7;
+  const bool zero_tile = M.dst > 0 && I - J >= M.dst;  // outside the DST band
+  if (zero_tile && !fill_zero) return;
+  const int r = threadIdx.x & 127, c0 = part * ncol + (threadIdx.x >> 7);
   const int64_t gi = I * ts + u * BLK + r;
   const bool ipad = gi >= nreal;
   const double xi = ipad ? 0.0 : xs[gi], yi = ipad ? 0.0 : ys[gi];
@@ -128,8 +158,7 @@ __global__ __launch_bounds__(256) void k_gen_tiles(TileMat M, int T, int64_t nre
   } else {
     out16 = (uint16_t*)((float*)M.off + off_index(I, J, M.NT) * ts * ts) + o;
   }
-  const bool zero_tile = M.dst > 0 && I - J >= M.dst;  // outside the DST band
-  for (int c = c0; c < BLK; c += 2) {
+  for (int c = c0; c < (part + 1) * ncol; c += 2) {
     const int64_t gj = J * ts + v * BLK + c;
     double val;
     if (zero_tile) {
@@ -162,23 +191,26 @@ __global__ __launch_bounds__(256) void k_gen_dense(double* __restrict__ cov, int
 int64_t quad_table_doubles() { return QT_TOTAL; }
 
 // qt: QT_TOTAL doubles (quadrature nodes, then the Chebyshev tables)
-void launch_quad_table(const double theta[3], int metric, double nugget, double* qt, double* cst, hipStream_t s) {
+void launch_quad_table(const double theta[3], int metric, double nugget, double* qt, double* cst,
+                       unsigned long long* info, hipStream_t s) {
   hipLaunchKernelGGL(k_quad_table, dim3(QNB), dim3(QNK), 0, s, theta[0], theta[1], theta[2], (double)metric, nugget,
-                     qt, cst);
-  hipLaunchKernelGGL(k_cheb_table, dim3(CH_NSEG), dim3(64), 0, s, qt, (const double*)cst);
+                     qt, cst, info);
+  hipLaunchKernelGGL(k_cheb_table, dim3(CH_NSEG), dim3(256), 0, s, qt, (const double*)cst);
 }
 
 void launch_gen_tiles(const TileMat& M, int64_t nreal, const double* xs, const double* ys, const double* qt,
-                      const double* cst, const uint8_t* tag, hipStream_t s) {
+                      const double* cst, const uint8_t* tag, bool fill_zero, hipStream_t s) {
   const int64_t ts = M.ts, NT = M.NT;
   const int T = (int)(ts / BLK);
   const int64_t ntile = NT * (NT + 1) / 2;
+  const int64_t R = (nreal + BLK - 1) / BLK;  // 128-blocks with real rows
+  const int parts = R * (R + 1) / 2 < 2048 ? 8 : 1;
   // keep each launch's grid below 2^31 blocks
-  const int64_t per = (int64_t)1 << 24;
+  const int64_t per = ((int64_t)1 << 30) / (T * T * parts);
   for (int64_t f = 0; f < ntile; f += per) {
     const int64_t cnt = (ntile - f < per) ? ntile - f : per;
-    hipLaunchKernelGGL(k_gen_tiles, dim3((unsigned)(cnt * T * T)), dim3(256), 0, s, M, T, nreal, xs, ys, qt, cst, tag,
-                       f);
+    hipLaunchKernelGGL(k_gen_tiles, dim3((unsigned)(cnt * T * T * parts)), dim3(256), 0, s, M, T, nreal, xs, ys, qt,
+                       cst, tag, f, parts, (int)fill_zero);
   }
 }
 

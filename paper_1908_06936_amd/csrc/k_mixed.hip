@@ -901,18 +901,20 @@ void launch_update_lp(const TileMat& M, const uint8_t* tag, const float* p32, co
                      off, (int)skip_bf16);
 }
 
+void launch_solve_below_lp(const TileMat& M, const uint8_t* tag, int64_t k, int64_t nreal, const double* y,
+                           double* rhs, hipStream_t s) {
+  const int64_t ts = M.ts, g0 = (k + 1) * (ts / BLK), gmax = (nreal + BLK - 1) / BLK;
+  if (gmax > g0)
+    hipLaunchKernelGGL(k_gemv_fwd_lp, dim3((unsigned)(gmax - g0)), dim3(SOLVE_THREADS),
+                       (size_t)(ts + SOLVE_THREADS) * sizeof(double), s, M, tag, k, g0, y + k * ts, rhs);
+}
+
 void launch_trsv_fwd_lp(const TileMat& M, const uint8_t* tag, const double* Xd, int64_t nreal, double* rhs,
                         double* y, hipStream_t s) {
   const int64_t ts = M.ts, NT = M.NT;
-  const int T = (int)(ts / BLK);
-  const size_t shm = (size_t)(ts + SOLVE_THREADS) * sizeof(double);
-  const int64_t gmax = (nreal + BLK - 1) / BLK;
   for (int64_t k = 0; k < NT; ++k) {
     launch_diag_apply_n(Xd + k * ts * ts, ts, rhs + k * ts, y + k * ts, s);
-    const int64_t g0 = (k + 1) * T;
-    if (gmax > g0)
-      hipLaunchKernelGGL(k_gemv_fwd_lp, dim3((unsigned)(gmax - g0)), dim3(SOLVE_THREADS), shm, s, M, tag, k, g0,
-                         y + k * ts, rhs);
+    launch_solve_below_lp(M, tag, k, nreal, y, rhs, s);
   }
 }
 

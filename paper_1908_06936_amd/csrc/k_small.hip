@@ -60,10 +60,12 @@ __device__ __forceinline__ uint32_t spread16(uint32_t v) {
 
 // key = Morton code of the 16-bit quantised location (high 32 bits) and the
 // caller index (low 32 bits), so keys are distinct and the order is unique.
+// rank (may be null): cleared for k_rank.
 __global__ void k_morton(const double* __restrict__ x, const double* __restrict__ y, int64_t n, int64_t P,
-                         const double* __restrict__ box, uint64_t* __restrict__ keys) {
+                         const double* __restrict__ box, uint64_t* __restrict__ keys, int32_t* __restrict__ rank) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= P) return;
+  if (rank && i < n) rank[i] = 0;
   if (i >= n) {
     keys[i] = ~(uint64_t)0;
     return;
@@ -135,6 +137,39 @@ __global__ void k_gather(const double* __restrict__ x, const double* __restrict_
     ys[i] = 0.0;
     if (zs) zs[i] = 0.0;
   }
+}
+
+// rank[i] += number of keys among RT of them (block y's) below key i.  The keys
+// are distinct, so the ranks are the places in the sorted order.  n^2 / 2 key
+// comparisons, but one launch: the bitonic network's launches are bound by
+// latency (n = 400: 28 us in one workgroup; n = 10,000: ten launches, 64 us).
+constexpr int RT = 512;
+__global__ __launch_bounds__(256) void k_rank(const uint64_t* __restrict__ keys, int64_t n,
+                                              int32_t* __restrict__ rank) {
+  __shared__ uint64_t sk[RT];
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x, j0 = (int64_t)blockIdx.y * RT;
+  for (int q = threadIdx.x; q < RT; q += 256) sk[q] = j0 + q < n ? keys[j0 + q] : ~(uint64_t)0;
+  __syncthreads();
+  if (i >= n) return;
+  const uint64_t key = keys[i];
+  int c = 0;
+#pragma unroll 8
+  for (int q = 0; q < RT; ++q) c += sk[q] < key;
+  if (c) atomicAdd(rank + i, c);
+}
+
+// k_gather from the ranks
+__global__ void k_rank_gather(const double* __restrict__ x, const double* __restrict__ y,
+                              const double* __restrict__ z, int64_t n, int64_t npad, const int32_t* __restrict__ rank,
+                              double* __restrict__ xs, double* __restrict__ ys, double* __restrict__ zs,
+                              int32_t* __restrict__ perm) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= npad) return;
+  const int64_t o = i < n ? rank[i] : i;
+  perm[o] = i < n ? (int32_t)i : -1;
+  xs[o] = i < n ? x[i] : 0.0;
+  ys[o] = i < n ? y[i] : 0.0;
+  if (zs) zs[o] = i < n && z ? z[i] : 0.0;
 }
 
 // out[perm[i]] = v[i] for i < n
@@ -418,7 +453,64 @@ __global__ __launch_bounds__(512, 4) void k_potrf_blk(
   }
 }
 
+// factor blocks that lie in the padding (the identity): their inverses (row
+// by row) and log-determinant parts, block blockIdx.x of dinv / ldpart
+__global__ __launch_bounds__(256) void k_pad_blk(double* __restrict__ dinv, double* __restrict__ ldpart) {
+  double* X = dinv + (int64_t)blockIdx.x * BLK * BLK;
+  for (int e = threadIdx.x; e < BLK * BLK; e += 256) X[e] = e / BLK == e % BLK ? 1.0 : 0.0;
+  if (threadIdx.x == 0) ldpart[blockIdx.x] = 0.0;
+}
+
 // ------------------------------------------------------- triangular solves
+// Forward substitution on one diagonal tile, y = L_kk^-1 rhs, by the 128-blocks
+// and their inverses (nblk blocks with real rows; y = 0 on the others): one
+// workgroup, bound by the latency of reading the tile's lower half from the L2.
+__global__ __launch_bounds__(1024) void k_tile_fwd(const double* __restrict__ L, int64_t ts,
+                                                   const double* __restrict__ dinv, const double* __restrict__ rhs,
+                                                   double* __restrict__ y, int nblk) {
+  extern __shared__ double fy[];  // ts (y), 128 (right-hand side of a block), 1024
+  double* sb = fy + ts;
+  double* red = sb + BLK;
+  const int t = threadIdx.x, r = t & 127, h = t >> 7;
+  for (int q = t; q < ts; q += 1024) fy[q] = 0.0;
+  __syncthreads();
+  for (int c = 0; c < nblk; ++c) {
+    const double* Lr = L + c * BLK + r;
+    double s = 0.0;
+    int q = h;
+    for (; q < c * BLK; q += 128) {  // 16 loads in flight per thread
+      double v[16];
+#pragma unroll
+      for (int e = 0; e < 16; ++e) v[e] = Lr[(int64_t)(q + 8 * e) * ts];
+#pragma unroll
+      for (int e = 0; e < 16; ++e) s += v[e] * fy[q + 8 * e];
+    }
+    red[t] = s;
+    __syncthreads();
+    if (t < BLK) {
+      double a = 0.0;
+#pragma unroll
+      for (int g = 0; g < 8; ++g) a += red[g * BLK + t];
+      sb[t] = rhs[c * BLK + t] - a;
+    }
+    __syncthreads();
+    // y_c = X s, X row by row: eight lanes per row
+    {
+      const int row = t >> 3, l = t & 7;
+      const double* X = dinv + ((int64_t)c * BLK + row) * BLK;
+      double a = 0.0;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) a += X[8 * e + l] * sb[8 * e + l];
+      a += __shfl_xor(a, 4, 8);
+      a += __shfl_xor(a, 2, 8);
+      a += __shfl_xor(a, 1, 8);
+      if (l == 0) fy[c * BLK + row] = a;
+    }
+    __syncthreads();
+  }
+  for (int q = t; q < ts; q += 1024) y[q] = fy[q];
+}
+
 // rhs_i -= L_ik y_k for the 128-row blocks g0 <= g < gmax below tile k.
 __global__ __launch_bounds__(SOLVE_THREADS) void k_gemv_fwd(TileMat M, int64_t k, int64_t g0,
                                                            const double* __restrict__ yk, double* __restrict__ rhs) {
@@ -509,10 +601,18 @@ __global__ __launch_bounds__(256) void k_trmv_lower(TileMat M, const double* __r
 }
 
 // ------------------------------------------------------------- reductions
+// the first failed pivot and the bounding box / input check behind the results,
+// so that one copy brings everything to the host
+__device__ __forceinline__ void append_status(double* out, const unsigned long long* info, const double* box) {
+  out[OUT_INFO] = __longlong_as_double((long long)*info);
+  for (int q = 0; q < 5; ++q) out[OUT_BOX + q] = box[q];
+}
+
 // out[0] = l, out[1] = log det, out[2] = y^T y  (eq. 2 with the true n)
 __global__ __launch_bounds__(256) void k_finalize_loglik(const double* __restrict__ yv, int64_t n,
                                                          const double* __restrict__ ldpart, int64_t nld,
-                                                         double* __restrict__ out) {
+                                                         const unsigned long long* __restrict__ info,
+                                                         const double* __restrict__ box, double* __restrict__ out) {
   __shared__ double red[2 * 256];
   double v[2] = {0.0, 0.0};
   for (int64_t i = threadIdx.x; i < n; i += 256) v[0] += yv[i] * yv[i];
@@ -523,6 +623,7 @@ __global__ __launch_bounds__(256) void k_finalize_loglik(const double* __restric
     out[0] = -0.5 * ((double)n * 1.8378770664093454836 + ld + q);
     out[1] = ld;
     out[2] = q;
+    append_status(out, info, box);
   }
 }
 
@@ -530,6 +631,8 @@ __global__ __launch_bounds__(256) void k_finalize_loglik(const double* __restric
 // z^T Sigma^-1 z = z^T a with a = Sigma^-1 z (refined solve)
 __global__ __launch_bounds__(256) void k_finalize_loglik_za(const double* __restrict__ zs, const double* __restrict__ av,
                                                             int64_t n, const double* __restrict__ ldpart, int64_t nld,
+                                                            const unsigned long long* __restrict__ info,
+                                                            const double* __restrict__ box,
                                                             double* __restrict__ out) {
   __shared__ double red[2 * 256];
   double v[2] = {0.0, 0.0};
@@ -541,6 +644,7 @@ __global__ __launch_bounds__(256) void k_finalize_loglik_za(const double* __rest
     out[0] = -0.5 * ((double)n * 1.8378770664093454836 + ld + q);
     out[1] = ld;
     out[2] = q;
+    append_status(out, info, box);
   }
 }
 
@@ -600,8 +704,6 @@ __global__ __launch_bounds__(256) void k_finalize_grad(const double* __restrict_
 }
 
 // ------------------------------------------------------------ fills/copies
-__global__ void k_fill_u64(unsigned long long* p, unsigned long long v) { *p = v; }
-
 __global__ void k_copy_f64(double* __restrict__ dst, const double* __restrict__ src, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) dst[i] = src[i];
@@ -631,10 +733,17 @@ __global__ void k_put_dinv(double* __restrict__ dst, const double* __restrict__ 
 static inline unsigned nb(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
 
 void launch_sort_locations(const double* x, const double* y, const double* z, int64_t n, int64_t npad, int64_t P,
-                           double* box, uint64_t* keys, double* xs, double* ys, double* zs, int32_t* perm,
-                           hipStream_t s) {
+                           double* box, uint64_t* keys, int32_t* rank, double* xs, double* ys, double* zs,
+                           int32_t* perm, hipStream_t s) {
   hipLaunchKernelGGL(k_bbox, dim3(1), dim3(1024), 0, s, x, y, z, n, box);
-  hipLaunchKernelGGL(k_morton, dim3(nb(P, 256)), dim3(256), 0, s, x, y, n, P, box, keys);
+  // ranks by counting up to 16,384 points (20 us there; the bitonic network 75 us)
+  if (n <= 16384) {
+    hipLaunchKernelGGL(k_morton, dim3(nb(n, 256)), dim3(256), 0, s, x, y, n, n, box, keys, rank);
+    hipLaunchKernelGGL(k_rank, dim3(nb(n, 256), nb(n, RT)), dim3(256), 0, s, keys, n, rank);
+    hipLaunchKernelGGL(k_rank_gather, dim3(nb(npad, 256)), dim3(256), 0, s, x, y, z, n, npad, rank, xs, ys, zs, perm);
+    return;
+  }
+  hipLaunchKernelGGL(k_morton, dim3(nb(P, 256)), dim3(256), 0, s, x, y, n, P, box, keys, (int32_t*)nullptr);
   // P is a power of two >= 2048
   hipLaunchKernelGGL(k_bitonic_local, dim3((unsigned)(P / 2048)), dim3(1024), 0, s, keys, (int64_t)2, (int64_t)2048,
                      (int64_t)1);
@@ -656,18 +765,26 @@ void launch_potrf_blk(double* A, int64_t lda, double* dinv, double* ldpart, unsi
   hipLaunchKernelGGL(k_potrf_blk, dim3(1), dim3(512), POTRF_LDS, s, A, lda, dinv, ldpart, info, col0);
 }
 
-void launch_trsv_fwd(const TileMat& M, const double* Xd, int64_t nreal, double* rhs, double* y, hipStream_t s) {
-  const int64_t ts = M.ts, NT = M.NT;
-  const int T = (int)(ts / BLK);
-  const size_t shm = (size_t)(ts + SOLVE_THREADS) * sizeof(double);
-  const int64_t gmax = (nreal + BLK - 1) / BLK;  // row blocks holding real rows
-  for (int64_t k = 0; k < NT; ++k) {
-    launch_diag_apply_n(Xd + k * ts * ts, ts, rhs + k * ts, y + k * ts, s);
-    const int64_t g0 = (k + 1) * T;
-    if (gmax > g0)
-      hipLaunchKernelGGL(k_gemv_fwd, dim3((unsigned)(gmax - g0)), dim3(SOLVE_THREADS), shm, s, M, k, g0, y + k * ts,
-                         rhs);
-  }
+void launch_pad_blocks(double* dinv, double* ldpart, int64_t count, hipStream_t s) {
+  if (count > 0) hipLaunchKernelGGL(k_pad_blk, dim3((unsigned)count), dim3(256), 0, s, dinv, ldpart);
+}
+
+void launch_solve_tile(const TileMat& M, int64_t k, const double* dinv_k, int64_t nreal, const double* rhs, double* y,
+                       hipStream_t s) {
+  const int64_t ts = M.ts, T = ts / BLK, gmax = (nreal + BLK - 1) / BLK;
+  const int nblk = (int)(gmax - k * T < T ? gmax - k * T : T);
+  hipLaunchKernelGGL(k_tile_fwd, dim3(1), dim3(1024), (size_t)(ts + BLK + 1024) * sizeof(double), s,
+                     (const double*)(M.diag + k * ts * ts), ts, dinv_k, rhs + k * ts, y + k * ts, nblk);
+}
+
+void launch_solve_below(const TileMat& M, int64_t k, int64_t nreal, const double* y, double* rhs, hipStream_t s) {
+  const int64_t ts = M.ts, T = ts / BLK;
+  int64_t gmax = (nreal + BLK - 1) / BLK;  // row blocks holding real rows
+  if (M.dst > 0 && gmax > (k + M.dst) * T) gmax = (k + M.dst) * T;  // zero below the band
+  const int64_t g0 = (k + 1) * T;
+  if (gmax > g0)
+    hipLaunchKernelGGL(k_gemv_fwd, dim3((unsigned)(gmax - g0)), dim3(SOLVE_THREADS),
+                       (size_t)(ts + SOLVE_THREADS) * sizeof(double), s, M, k, g0, y + k * ts, rhs);
 }
 
 void launch_diag_apply_n(const double* Xk, int64_t ts, const double* b, double* out, hipStream_t s) {
@@ -693,14 +810,14 @@ void launch_trmv_lower(const TileMat& M, int64_t nreal, const double* e, double*
   hipLaunchKernelGGL(k_trmv_lower, dim3((unsigned)gmax), dim3(256), 0, s, M, e, w);
 }
 
-void launch_finalize_loglik(const double* yv, int64_t n, const double* ldpart, int64_t nld, double* out,
-                            hipStream_t s) {
-  hipLaunchKernelGGL(k_finalize_loglik, dim3(1), dim3(256), 0, s, yv, n, ldpart, nld, out);
+void launch_finalize_loglik(const double* yv, int64_t n, const double* ldpart, int64_t nld,
+                            const unsigned long long* info, const double* box, double* out, hipStream_t s) {
+  hipLaunchKernelGGL(k_finalize_loglik, dim3(1), dim3(256), 0, s, yv, n, ldpart, nld, info, box, out);
 }
 
 void launch_finalize_loglik_za(const double* zs, const double* av, int64_t n, const double* ldpart, int64_t nld,
-                               double* out, hipStream_t s) {
-  hipLaunchKernelGGL(k_finalize_loglik_za, dim3(1), dim3(256), 0, s, zs, av, n, ldpart, nld, out);
+                               const unsigned long long* info, const double* box, double* out, hipStream_t s) {
+  hipLaunchKernelGGL(k_finalize_loglik_za, dim3(1), dim3(256), 0, s, zs, av, n, ldpart, nld, info, box, out);
 }
 
 void launch_add2(double* y, const double* a, const double* d, int64_t n, hipStream_t s) {
@@ -718,10 +835,6 @@ void launch_refine_select(double* a, const double* a_try, double* r, const doubl
 
 void launch_finalize_grad(const double* part, int64_t nparts, double* out, hipStream_t s) {
   hipLaunchKernelGGL(k_finalize_grad, dim3(1), dim3(256), 0, s, part, nparts, out);
-}
-
-void launch_fill_info(unsigned long long* info, hipStream_t s) {
-  hipLaunchKernelGGL(k_fill_u64, dim3(1), dim3(1), 0, s, info, ~0ull);
 }
 
 void launch_copy(double* dst, const double* src, int64_t n, hipStream_t s) {

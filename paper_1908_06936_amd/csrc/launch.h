@@ -45,9 +45,11 @@ inline int block_tiles_uneven(int64_t nb) { return nb >= 1536 ? 4 : (nb >= 64 ? 
 // k_matern.hip
 // doubles of the per-theta table array (quadrature nodes + Chebyshev tables)
 int64_t quad_table_doubles();
-void launch_quad_table(const double theta[3], int metric, double nugget, double* qt, double* cst, hipStream_t s);
+// info (may be null): reset to "no failed pivot"
+void launch_quad_table(const double theta[3], int metric, double nugget, double* qt, double* cst,
+                       unsigned long long* info, hipStream_t s);
 void launch_gen_tiles(const TileMat& M, int64_t nreal, const double* xs, const double* ys, const double* qt,
-                      const double* cst, const uint8_t* tag, hipStream_t s);
+                      const double* cst, const uint8_t* tag, bool fill_zero, hipStream_t s);
 void launch_gen_dense(double* cov, int64_t ldc, int64_t n, const double* x, const double* y, const double* qt,
                       const double* cst, hipStream_t s);
 // r = z - Sigma a in FP64 (Sigma regenerated), sorted order, zero on padding
@@ -56,20 +58,31 @@ void launch_sigma_residual(const double* xs, const double* ys, const double* zs,
 
 // k_small.hip
 void launch_sort_locations(const double* x, const double* y, const double* z, int64_t n, int64_t npad, int64_t P,
-                           double* box, uint64_t* keys, double* xs, double* ys, double* zs, int32_t* perm,
-                           hipStream_t s);
+                           double* box, uint64_t* keys, int32_t* rank, double* xs, double* ys, double* zs,
+                           int32_t* perm, hipStream_t s);
 void launch_scatter(const double* v, const int32_t* perm, int64_t n, double* out, hipStream_t s);
 void launch_potrf_blk(double* A, int64_t lda, double* dinv, double* ldpart, unsigned long long* info, int64_t col0,
                       hipStream_t s);
-void launch_trsv_fwd(const TileMat& M, const double* Xd, int64_t nreal, double* rhs, double* y, hipStream_t s);
+// inverses and log-determinant parts of `count` factor blocks in the padding
+void launch_pad_blocks(double* dinv, double* ldpart, int64_t count, hipStream_t s);
+// forward solve by tiles: y_k = L_kk^-1 rhs_k from the 128-block inverses of
+// tile k, then rhs_i -= L_ik y_k below it
+void launch_solve_tile(const TileMat& M, int64_t k, const double* dinv_k, int64_t nreal, const double* rhs, double* y,
+                       hipStream_t s);
+void launch_solve_below(const TileMat& M, int64_t k, int64_t nreal, const double* y, double* rhs, hipStream_t s);
+void launch_solve_below_lp(const TileMat& M, const uint8_t* tag, int64_t k, int64_t nreal, const double* y,
+                           double* rhs, hipStream_t s);
 void launch_trsv_bwd(const TileMat& M, const double* Xd, double* rhs, double* a, hipStream_t s);
 void launch_trmv_lower(const TileMat& M, int64_t nreal, const double* e, double* w, hipStream_t s);
-void launch_finalize_loglik(const double* yv, int64_t n, const double* ldpart, int64_t nld, double* out,
-                            hipStream_t s);
+// out[0..2] = l, log det, quadratic form; out[OUT_INFO], out[OUT_BOX ..] the
+// first failed pivot (as an integer) and box[0..4]
+enum { OUT_INFO = 6, OUT_BOX = 7, OUT_COUNT = 12 };
+void launch_finalize_loglik(const double* yv, int64_t n, const double* ldpart, int64_t nld,
+                            const unsigned long long* info, const double* box, double* out, hipStream_t s);
 void launch_finalize_grad(const double* part, int64_t nparts, double* out, hipStream_t s);
 // eq. (2) with the quadratic form z^T a (a = Sigma^-1 z)
 void launch_finalize_loglik_za(const double* zs, const double* av, int64_t n, const double* ldpart, int64_t nld,
-                               double* out, hipStream_t s);
+                               const unsigned long long* info, const double* box, double* out, hipStream_t s);
 // refinement steps on the device: y = a + d; nrm[0] = |r|^2 (trial = 0) or
 // nrm[1] = (|r|^2 < nrm[0]) with nrm[0] lowered then (trial = 1); the select
 // takes a_try, r_try when nrm[1] is set
@@ -77,7 +90,6 @@ void launch_add2(double* y, const double* a, const double* d, int64_t n, hipStre
 void launch_resid_norm(const double* r, int64_t n, double* nrm, int trial, hipStream_t s);
 void launch_refine_select(double* a, const double* a_try, double* r, const double* r_try, const double* nrm,
                           int64_t n, hipStream_t s);
-void launch_fill_info(unsigned long long* info, hipStream_t s);
 void launch_copy(double* dst, const double* src, int64_t n, hipStream_t s);
 void launch_copy_diag_lower(double* dst, const double* diag, int64_t ts, int64_t NT, hipStream_t s);
 void launch_put_dinv(double* dst, const double* dinv, int64_t ts, int64_t NT, int c, hipStream_t s);

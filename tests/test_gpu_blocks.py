@@ -88,3 +88,39 @@ def test_fisher_block_widths(orc, exa, n, ts, nugget):
     got = ctx.fisher(dev(x), dev(y), th)
     d = np.sqrt(np.diag(ref))
     assert np.max(np.abs(got - ref) / np.outer(d, d)) <= 1e-9
+
+
+# the order of the locations by counting (up to 16,384 points) and by the
+# bitonic network above: the sorted problem, and so every bit of l, does not
+# depend on the caller's order
+@pytest.mark.parametrize("n", [1, 255, 257, 511, 513, 2049, 16384, 16385])
+def test_order_does_not_depend_on_the_callers(exa, n):
+    ctx = exa.Context(ts=1024)
+    ctx.set_dst_band(2)  # zeroes tiles by the order, and keeps the large ones cheap
+    x, y = inputgen.uniform(n, seed=600 + n)
+    z = inputgen.smooth_field(x, y, seed=n)
+    th = [1.0, 0.002, 0.5]
+    a = ctx.loglik(dev(x), dev(y), dev(z), th)
+    p = inputgen.shuffled(n, seed=n)
+    b = ctx.loglik(dev(x[p]), dev(y[p]), dev(z[p]), th)
+    assert np.isfinite(a) and a == b
+
+
+# DST likelihoods after other work has filled the workspace: the tiles outside
+# the band are neither read nor written
+@pytest.mark.parametrize("n,band", [(700, 1), (900, 2), (1000, 3)])
+def test_dst_ignores_what_lies_outside_the_band(orc, exa, n, band):
+    ctx = exa.Context(ts=128)
+    x, y = inputgen.jittered_grid(32, seed=n)
+    x, y = x[:n], y[:n]
+    th = [1.0, 0.01, 0.5]
+    z = inputgen.smooth_field(x, y, seed=n)
+    X, Y, Z = dev(x), dev(y), dev(z)
+    ctx.loglik_grad(X, Y, Z, [1.0, 0.1, 1.0])
+    ctx.set_dst_band(band)
+    ref = orc.loglik_dst(x, y, z, th, 128, band)
+    assert ctx.loglik(X, Y, Z, th) == pytest.approx(ref, rel=1e-10)
+    ll, g = ctx.loglik_grad(X, Y, Z, th)
+    ll_ref, g_ref = orc.loglik_grad_dst(x, y, z, th, 128, band)
+    assert ll == pytest.approx(ll_ref, rel=1e-10)
+    assert_score_close(g, g_ref, n, th)
