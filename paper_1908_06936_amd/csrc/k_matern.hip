@@ -56,12 +56,15 @@ __global__ void k_quad_table(double s2, double beta, double nu, double metric, d
 // are its value at the segment centre (the middle point, t = 0) and the
 // Chebyshev coefficients of ln(u / u_centre), c_k = (2/N) sum_j d_j
 // cos(pi k (j + 1/2) / N), whose magnitudes stay small.  Runs after
-// k_quad_table.  Bound by latency: 16 lanes share the up to 400 nodes of one
-// point and the logarithms and cosines are formed once, one per thread
-// (68 us with a thread per point and per coefficient, 12 us so).
+// k_quad_table.  Bound by latency: 16 lanes share the exponentials of the up to
+// 400 nodes of one point, one thread per function then adds them in node order
+// (so the table does not depend on the split), and the logarithms and cosines
+// are formed once, one per thread.  With a thread per point and per
+// coefficient: 68 us.
 __global__ __launch_bounds__(256) void k_cheb_table(double* __restrict__ qt, const double* __restrict__ cst) {
   constexpr int LP = 16;  // lanes per point
-  __shared__ double fv[3][CH_N], lg[3][CH_N], cs[CH_N][CH_N];
+  __shared__ double fv[3][CH_N], lg[3][CH_N], cs[CH_N][CH_N], ex[CH_N][QNK + 1], xs[CH_N];
+  __shared__ int nk[CH_N];
   const int seg = blockIdx.x, t = threadIdx.x;
   const double pi = 3.14159265358979323846;
   const double nu = cst[C_NU];
@@ -71,26 +74,31 @@ __global__ __launch_bounds__(256) void k_cheb_table(double* __restrict__ qt, con
     const double tj = cos(pi * (j + 0.5) / CH_N);
     const double x = exp(CH_SLO + (seg + 0.5 * (tj + 1.0)) * CH_DS);
     const double* q = qt + (quad_bucket(x) * QNK + l) * QW;
-    double a = 0.0, b = 0.0, c2 = 0.0;
-    for (int k = l; k < QNK; k += LP, q += LP * QW) {
+    int k = l;
+    for (; k < QNK; k += LP, q += LP * QW) {
       const double c = q[0];
       if (k > 0 && x * c - nu * q[1] > QCUT + 5.0) break;
-      const double e = exp(-x * c);
-      a += e * q[2];
-      b += e * q[3];
-      c2 += e * q[4];
+      ex[j][k] = exp(-x * c);
     }
-    for (int o = LP / 2; o > 0; o >>= 1) {
-      a += __shfl_xor(a, o, LP);
-      b += __shfl_xor(b, o, LP);
-      c2 += __shfl_xor(c2, o, LP);
+    for (int o = LP / 2; o > 0; o >>= 1) k = min(k, __shfl_xor(k, o, LP));
+    if (l == 0) xs[j] = x, nk[j] = min(k, QNK);
+  }
+  __syncthreads();
+  if (t < 3 * CH_N) {
+    const int f = t / CH_N, j = t % CH_N, n = nk[j];
+    const double x = xs[j], xn = pow(x, nu);
+    const double* q = qt + quad_bucket(x) * QNK * QW + 2 + f;
+    double a = 0.0;
+    int k = 0;
+    for (; k + 8 <= n; k += 8) {
+      double v[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = q[(k + e) * QW];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) a += ex[j][k + e] * v[e];
     }
-    if (l == 0) {
-      const double xn = pow(x, nu);
-      fv[0][j] = xn * a;
-      fv[1][j] = xn * x * b;
-      fv[2][j] = xn * c2;
-    }
+    for (; k < n; ++k) a += ex[j][k] * q[k * QW];
+    fv[f][j] = f == 1 ? xn * x * a : xn * a;
   }
   __syncthreads();
   if (t < 3 * CH_N) lg[t / CH_N][t % CH_N] = log(fv[t / CH_N][t % CH_N] / fv[t / CH_N][CH_MID]);
