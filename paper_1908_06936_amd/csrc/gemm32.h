@@ -39,117 +39,102 @@ __device__ __forceinline__ v16f mfma32x32(float x, float y, v16f c) {
 }
 
 // One operand's share of a stage (G32_BK k values x 128 rows) for one thread,
-// held in registers between the global load and the LDS store.  p points at
-// Op(0, k0); KC = false: Op(m, k0 + q) = p[m + q ld]; KC = true: p[q + m ld].
+// NP pieces of 16 bytes, held in registers between the global load and the LDS
+// store.  KC = false: Op(m, k0 + q) = p[m + q ld]; KC = true: p[q + m ld], p the
+// (uniform) address behind the buffer resource.  Every piece is at the thread's
+// byte offset off(ld, t) plus the uniform s step(ld).
 template <int SK, bool KC>
 struct Stage32;
 
+__device__ __forceinline__ u4 stage_load16(__amdgpu_buffer_rsrc_t g, uint32_t off, uint32_t soff) {
+  return __builtin_amdgcn_raw_buffer_load_b128(g, (int)off, (int)soff, 0);
+}
+
 template <>
 struct Stage32<SRC_F32, false> {
-  f4 r[2];
-  __device__ __forceinline__ void load(const void* p, int64_t ld, int t) {
-    const float* a = (const float*)p;
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const int idx = t + 256 * s, kk = idx >> 5, m4 = idx & 31;
-      r[s] = *(const f4*)(a + 4 * m4 + (int64_t)kk * ld);
-    }
+  static constexpr int NP = 2;
+  f4 r[NP];
+  static __device__ __forceinline__ uint32_t off(uint32_t ld, int t) { return 16u * (t & 31) + 4u * (t >> 5) * ld; }
+  static __device__ __forceinline__ uint32_t step(uint32_t ld) { return 32u * ld; }
+  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t g, uint32_t o, uint32_t st, int s) {
+    r[s] = __builtin_bit_cast(f4, stage_load16(g, o, s * st));
   }
-  __device__ __forceinline__ void store(float* S, int t) const {
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const int idx = t + 256 * s, kk = idx >> 5, m4 = idx & 31;
-      *(f4*)(S + kk * G32_LDP + 4 * m4) = r[s];
-    }
+  __device__ __forceinline__ void store(float* S, int t, int s) const {
+    *(f4*)(S + ((t >> 5) + 8 * s) * G32_LDP + 4 * (t & 31)) = r[s];
   }
 };
 
 template <>
 struct Stage32<SRC_F32, true> {
-  f4 r[2];
-  __device__ __forceinline__ void load(const void* p, int64_t ld, int t) {
-    const float* a = (const float*)p;
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const int idx = t + 256 * s, m = idx >> 2, k4 = idx & 3;
-      r[s] = *(const f4*)(a + 4 * k4 + (int64_t)m * ld);
-    }
+  static constexpr int NP = 2;
+  f4 r[NP];
+  static __device__ __forceinline__ uint32_t off(uint32_t ld, int t) { return 16u * (t & 3) + 4u * (t >> 2) * ld; }
+  static __device__ __forceinline__ uint32_t step(uint32_t ld) { return 256u * ld; }
+  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t g, uint32_t o, uint32_t st, int s) {
+    r[s] = __builtin_bit_cast(f4, stage_load16(g, o, s * st));
   }
-  __device__ __forceinline__ void store(float* S, int t) const {
+  __device__ __forceinline__ void store(float* S, int t, int s) const {
+    float* q = S + 4 * (t & 3) * G32_LDP + (t >> 2) + 64 * s;
 #pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const int idx = t + 256 * s, m = idx >> 2, k4 = idx & 3;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) S[(4 * k4 + e) * G32_LDP + m] = r[s][e];
-    }
+    for (int e = 0; e < 4; ++e) q[e * G32_LDP] = r[s][e];
   }
 };
 
 template <>
 struct Stage32<SRC_F64, false> {
-  d2 r[4];
-  __device__ __forceinline__ void load(const void* p, int64_t ld, int t) {
-    const double* a = (const double*)p;
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const int idx = t + 256 * s, kk = idx >> 6, m2 = idx & 63;
-      r[s] = *(const d2*)(a + 2 * m2 + (int64_t)kk * ld);
-    }
+  static constexpr int NP = 4;
+  d2 r[NP];
+  static __device__ __forceinline__ uint32_t off(uint32_t ld, int t) { return 16u * (t & 63) + 8u * (t >> 6) * ld; }
+  static __device__ __forceinline__ uint32_t step(uint32_t ld) { return 32u * ld; }
+  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t g, uint32_t o, uint32_t st, int s) {
+    r[s] = __builtin_bit_cast(d2, stage_load16(g, o, s * st));
   }
-  __device__ __forceinline__ void store(float* S, int t) const {
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const int idx = t + 256 * s, kk = idx >> 6, m2 = idx & 63;
-      f2 v;
-      v.x = (float)r[s].x;
-      v.y = (float)r[s].y;
-      *(f2*)(S + kk * G32_LDP + 2 * m2) = v;
-    }
+  __device__ __forceinline__ void store(float* S, int t, int s) const {
+    f2 v;
+    v.x = (float)r[s].x;
+    v.y = (float)r[s].y;
+    *(f2*)(S + ((t >> 6) + 4 * s) * G32_LDP + 2 * (t & 63)) = v;
   }
 };
 
 template <>
 struct Stage32<SRC_F64, true> {
-  d2 r[4];
-  __device__ __forceinline__ void load(const void* p, int64_t ld, int t) {
-    const double* a = (const double*)p;
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const int idx = t + 256 * s, m = idx >> 3, k2 = idx & 7;
-      r[s] = *(const d2*)(a + 2 * k2 + (int64_t)m * ld);
-    }
+  static constexpr int NP = 4;
+  d2 r[NP];
+  static __device__ __forceinline__ uint32_t off(uint32_t ld, int t) { return 16u * (t & 7) + 8u * (t >> 3) * ld; }
+  static __device__ __forceinline__ uint32_t step(uint32_t ld) { return 256u * ld; }
+  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t g, uint32_t o, uint32_t st, int s) {
+    r[s] = __builtin_bit_cast(d2, stage_load16(g, o, s * st));
   }
-  __device__ __forceinline__ void store(float* S, int t) const {
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const int idx = t + 256 * s, m = idx >> 3, k2 = idx & 7;
-      S[(2 * k2) * G32_LDP + m] = (float)r[s].x;
-      S[(2 * k2 + 1) * G32_LDP + m] = (float)r[s].y;
-    }
+  __device__ __forceinline__ void store(float* S, int t, int s) const {
+    float* q = S + 2 * (t & 7) * G32_LDP + (t >> 3) + 32 * s;
+    q[0] = (float)r[s].x;
+    q[G32_LDP] = (float)r[s].y;
   }
 };
 
 template <>
 struct Stage32<SRC_BF16, false> {
-  u4 r;
-  __device__ __forceinline__ void load(const void* p, int64_t ld, int t) {
-    const uint16_t* a = (const uint16_t*)p;
-    const int kk = t >> 4, m8 = t & 15;
-    r = *(const u4*)(a + 8 * m8 + (int64_t)kk * ld);
+  static constexpr int NP = 1;
+  u4 r[NP];
+  static __device__ __forceinline__ uint32_t off(uint32_t ld, int t) { return 16u * (t & 15) + 2u * (t >> 4) * ld; }
+  static __device__ __forceinline__ uint32_t step(uint32_t) { return 0; }
+  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t g, uint32_t o, uint32_t, int) {
+    r[0] = stage_load16(g, o, 0);
   }
-  __device__ __forceinline__ void store(float* S, int t) const {
-    const int kk = t >> 4, m8 = t & 15;
+  __device__ __forceinline__ void store(float* S, int t, int) const {
+    const u4 h = r[0];
     f4 lo, hi;
-    lo.x = __uint_as_float(r.x << 16);
-    lo.y = __uint_as_float(r.x & 0xffff0000u);
-    lo.z = __uint_as_float(r.y << 16);
-    lo.w = __uint_as_float(r.y & 0xffff0000u);
-    hi.x = __uint_as_float(r.z << 16);
-    hi.y = __uint_as_float(r.z & 0xffff0000u);
-    hi.z = __uint_as_float(r.w << 16);
-    hi.w = __uint_as_float(r.w & 0xffff0000u);
-    *(f4*)(S + kk * G32_LDP + 8 * m8) = lo;
-    *(f4*)(S + kk * G32_LDP + 8 * m8 + 4) = hi;
+    lo.x = __uint_as_float(h.x << 16);
+    lo.y = __uint_as_float(h.x & 0xffff0000u);
+    lo.z = __uint_as_float(h.y << 16);
+    lo.w = __uint_as_float(h.y & 0xffff0000u);
+    hi.x = __uint_as_float(h.z << 16);
+    hi.y = __uint_as_float(h.z & 0xffff0000u);
+    hi.z = __uint_as_float(h.w << 16);
+    hi.w = __uint_as_float(h.w & 0xffff0000u);
+    *(f4*)(S + (t >> 4) * G32_LDP + 8 * (t & 15)) = lo;
+    *(f4*)(S + (t >> 4) * G32_LDP + 8 * (t & 15) + 4) = hi;
   }
 };
 
@@ -179,51 +164,83 @@ __device__ __forceinline__ void gemm32(AP aptr, int64_t lda, BP bptr, int64_t ld
   // two register sets: the global loads run two stages ahead of the MFMAs
   Stage32<SA, AKC> a0, a1;
   Stage32<SB, BKC> b0, b1;
-  auto compute = [&](int cur) {
-    const float* sa = sA + cur * G32_BK * G32_LDP + wr * 64 + (lane & 31);
-    const float* sb = sB + cur * G32_BK * G32_LDP + wc * 64 + (lane & 31);
+  const uint32_t oa = a0.off((uint32_t)lda, t), ob = b0.off((uint32_t)ldb, t);
+  const uint32_t da = a0.step((uint32_t)lda), db = b0.step((uint32_t)ldb);
+  constexpr int NPA = Stage32<SA, AKC>::NP, NPB = Stage32<SB, BKC>::NP;
+  // the products of k slice kk, kk + 1 of LDS buffer cur
+  auto slice = [&](int cur, int kk) {
+    const int ko = (cur * G32_BK + kk + (lane >> 5)) * G32_LDP + (lane & 31);
+    float af[2], bf[2];
 #pragma unroll
-    for (int kk = 0; kk < G32_BK; kk += 2) {
-      const int ko = (kk + (lane >> 5)) * G32_LDP;
-      float af[2], bf[2];
+    for (int x = 0; x < 2; ++x) af[x] = sA[ko + wr * 64 + 32 * x];
 #pragma unroll
-      for (int x = 0; x < 2; ++x) af[x] = sa[ko + 32 * x];
+    for (int y = 0; y < 2; ++y) bf[y] = sB[ko + wc * 64 + 32 * y];
 #pragma unroll
-      for (int y = 0; y < 2; ++y) bf[y] = sb[ko + 32 * y];
+    for (int x = 0; x < 2; ++x)
 #pragma unroll
-      for (int x = 0; x < 2; ++x)
-#pragma unroll
-        for (int y = 0; y < 2; ++y) acc[x][y] = mfma32x32(bf[y], af[x], acc[x][y]);
+      for (int y = 0; y < 2; ++y) acc[x][y] = mfma32x32(bf[y], af[x], acc[x][y]);
+  };
+  // one stage, as in gemm_core: the pieces of the loads and of the LDS stores
+  // dealt between the NS k slices, A's and B's apart (at n = 40,000 with the
+  // loads and the stores in one run each: k_tri_gemm_lp 166 -> 158 ms,
+  // k_lauum_contract_lp 145 -> 138 ms, k_update_lp 92 -> 88 ms)
+  auto stage = [&](auto fetch, int cur, int k0, Stage32<SA, AKC>& fa, Stage32<SB, BKC>& fb, const Stage32<SA, AKC>& pa,
+                   const Stage32<SB, BKC>& pb) {
+    constexpr bool FETCH = decltype(fetch)::value;
+    constexpr int NS = G32_BK / 2;
+    __amdgpu_buffer_rsrc_t ga, gb;
+    if constexpr (FETCH) {
+      ga = stage_rsrc(aptr(k0));
+      gb = stage_rsrc(bptr(k0));
     }
+    float* na = sA + (cur ^ 1) * G32_BK * G32_LDP;
+    float* nb = sB + (cur ^ 1) * G32_BK * G32_LDP;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      slice(cur, 2 * s);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int q = 0; q < NPA; ++q)
+        if (q * NS / NPA == s) {
+          if constexpr (FETCH) fa.load(ga, oa, da, q);
+          pa.store(na, t, q);
+        }
+#pragma unroll
+      for (int q = 0; q < NPB; ++q)
+        if (q * NS / NPB + 1 == s) {
+          if constexpr (FETCH) fb.load(gb, ob, db, q);
+          pb.store(nb, t, q);
+        }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    __syncthreads();
   };
   const int nst = K / G32_BK;  // even
-  a0.load(aptr(0), lda, t);
-  b0.load(bptr(0), ldb, t);
-  a1.load(aptr(G32_BK), lda, t);
-  b1.load(bptr(G32_BK), ldb, t);
-  a0.store(sA, t);
-  b0.store(sB, t);
-  __syncthreads();
-  for (int s = 0; s < nst; s += 2) {
-    if (s + 2 < nst) {
-      a0.load(aptr((s + 2) * G32_BK), lda, t);
-      b0.load(bptr((s + 2) * G32_BK), ldb, t);
-    }
-    compute(0);
-    a1.store(sA + G32_BK * G32_LDP, t);
-    b1.store(sB + G32_BK * G32_LDP, t);
-    __syncthreads();
-    if (s + 3 < nst) {
-      a1.load(aptr((s + 3) * G32_BK), lda, t);
-      b1.load(bptr((s + 3) * G32_BK), ldb, t);
-    }
-    compute(1);
-    if (s + 2 < nst) {
-      a0.store(sA, t);
-      b0.store(sB, t);
-    }
-    __syncthreads();
+  {
+    const __amdgpu_buffer_rsrc_t ga = stage_rsrc(aptr(0)), gb = stage_rsrc(bptr(0));
+    const __amdgpu_buffer_rsrc_t ga1 = stage_rsrc(aptr(G32_BK)), gb1 = stage_rsrc(bptr(G32_BK));
+#pragma unroll
+    for (int q = 0; q < NPA; ++q) a0.load(ga, oa, da, q);
+#pragma unroll
+    for (int q = 0; q < NPB; ++q) b0.load(gb, ob, db, q);
+#pragma unroll
+    for (int q = 0; q < NPA; ++q) a1.load(ga1, oa, da, q);
+#pragma unroll
+    for (int q = 0; q < NPB; ++q) b1.load(gb1, ob, db, q);
+#pragma unroll
+    for (int q = 0; q < NPA; ++q) a0.store(sA, t, q);
+#pragma unroll
+    for (int q = 0; q < NPB; ++q) b0.store(sB, t, q);
   }
+  __syncthreads();
+  for (int s = 0; s + 2 < nst; s += 2) {
+    stage(std::true_type{}, 0, (s + 2) * G32_BK, a0, b0, a1, b1);
+    stage(std::true_type{}, 1, (s + 3) * G32_BK, a1, b1, a0, b0);
+  }
+  stage(std::false_type{}, 0, 0, a0, b0, a1, b1);
+#pragma unroll
+  for (int kk = 0; kk < G32_BK; kk += 2) slice(1, kk);
+  __syncthreads();
 }
 
 // plain-pointer form: Op(0, k0) = base + k0 * (KC ? 1 : ld)
@@ -305,16 +322,21 @@ __device__ __forceinline__ void gemm_bf16(AP aptr, int64_t lda, BP bptr, int64_t
   gload(GB_BK, ra1, rb1);
   sstore(0, ra0, rb0);
   __syncthreads();
-  for (int s = 0; s < nst; s += 2) {
-    if (s + 2 < nst) gload((s + 2) * GB_BK, ra0, rb0);
+  for (int s = 0; s + 2 < nst; s += 2) {
+    gload((s + 2) * GB_BK, ra0, rb0);
     compute(0);
     sstore(1, ra1, rb1);
     __syncthreads();
-    if (s + 3 < nst) gload((s + 3) * GB_BK, ra1, rb1);
+    gload((s + 3) * GB_BK, ra1, rb1);
     compute(1);
-    if (s + 2 < nst) sstore(0, ra0, rb0);
+    sstore(0, ra0, rb0);
     __syncthreads();
   }
+  compute(0);
+  sstore(1, ra1, rb1);
+  __syncthreads();
+  compute(1);
+  __syncthreads();
 }
 
 }  // namespace exg

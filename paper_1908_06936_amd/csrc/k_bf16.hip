@@ -77,16 +77,21 @@ __device__ __forceinline__ void gemm_bf16_wide(AP aptr, int64_t lda, BP bptr, in
   gload(WB_BK, ra1, rb1);
   sstore(0, ra0, rb0);
   __syncthreads();
-  for (int s = 0; s < nst; s += 2) {
-    if (s + 2 < nst) gload((s + 2) * WB_BK, ra0, rb0);
+  for (int s = 0; s + 2 < nst; s += 2) {
+    gload((s + 2) * WB_BK, ra0, rb0);
     compute(0);
     sstore(1, ra1, rb1);
     __syncthreads();
-    if (s + 3 < nst) gload((s + 3) * WB_BK, ra1, rb1);
+    gload((s + 3) * WB_BK, ra1, rb1);
     compute(1);
-    if (s + 2 < nst) sstore(0, ra0, rb0);
+    sstore(0, ra0, rb0);
     __syncthreads();
   }
+  compute(0);
+  sstore(1, ra1, rb1);
+  __syncthreads();
+  compute(1);
+  __syncthreads();
 }
 
 // Step k, BF16 targets (li[e], lj[e]) for the list entries e0 <= e < e0 +

@@ -105,7 +105,7 @@ __global__ __launch_bounds__(256, 2) void k_fisher_xg(TileMat X, const double* _
     auto bp = [=](int k0) -> const double* {
       return S + (jj * NT + k0 / ts) * ts * ts + v * E + (int64_t)(k0 % ts) * ts;
     };
-    gemm_core<false, false, false, B, B>(ap, ts, bp, ts, (int)(I * ts + (u + 1) * E), acc, sm);
+    gemm_core<false, false, B, B>(ap, ts, bp, ts, (int)(I * ts + (u + 1) * E), acc, sm);
   }
   acc_store(low_tile(Bm, I, J, NT, ts) + u * E + (int64_t)v * E * ts, ts, acc, 1.0, false);
 }
@@ -138,7 +138,7 @@ __global__ __launch_bounds__(256, 2) void k_fisher_mxt(TileMat X, const double* 
     return low_tile((double*)Bm, I, k0 / ts, NT, ts) + u * E + (int64_t)(k0 % ts) * ts;
   };
   auto bp = [=](int k0) -> const double* { return tptr(X, J, k0 / ts) + v * E + (int64_t)(k0 % ts) * ts; };
-  gemm_core<false, false, false, B, B>(ap, ts, bp, ts, (int)(J * ts + (v + 1) * E), acc, sm);
+  gemm_core<false, false, B, B>(ap, ts, bp, ts, (int)(J * ts + (v + 1) * E), acc, sm);
   acc_store(stage + (jj * NT + I) * ts * ts + u * E + (int64_t)v * E * ts, ts, acc, 1.0, false);
 }
 

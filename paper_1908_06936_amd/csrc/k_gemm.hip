@@ -60,7 +60,7 @@ __global__ __launch_bounds__(256, 2) void k_chol_update(TileMat M, const double*
               (int64_t)v * E * ts;
   v4d acc[B][B];
   acc_zero(acc);
-  gemm_blk<false, false, true, B, B>(Ap, ts, Bp, ts, (int)ts, acc, sm);
+  gemm_blk<false, false, B, B>(Ap, ts, Bp, ts, (int)ts, acc, sm);
   acc_store(C, ts, acc, -1.0, true);
 }
 
@@ -86,7 +86,7 @@ __global__ __launch_bounds__(256, 2) void k_panel_update(double* __restrict__ Dk
   const double* D = Dk + c * BLK + pv * E;
   v4d acc[B][B];
   acc_zero(acc);
-  gemm_blk<false, false, true, B, B>(P, ts, D, ts, c * BLK, acc, sm);
+  gemm_blk<false, false, B, B>(P, ts, D, ts, c * BLK, acc, sm);
   acc_store(P + (int64_t)(c * BLK + pv * E) * ts, ts, acc, -1.0, true);
 }
 
@@ -105,7 +105,7 @@ __global__ __launch_bounds__(256, 2) void k_panel_trsm(double* __restrict__ Dk, 
   double* C = panel_tile(Dk, below, i, k, ts) + u * BLK + (int)(blockIdx.x % S) * E + (int64_t)c * BLK * ts;
   v4d acc[B][4];
   acc_zero(acc);
-  gemm_blk<false, true, false, B, 4>(C, ts, dinv, BLK, BLK, acc, sm);  // Bop(n, q) = X(n, q), X row by row
+  gemm_blk<false, true, B, 4>(C, ts, dinv, BLK, BLK, acc, sm);  // Bop(n, q) = X(n, q), X row by row
   acc_store(C, ts, acc, 1.0, false);
 }
 
@@ -125,7 +125,7 @@ __global__ __launch_bounds__(256, 2) void k_dinv_right(double* __restrict__ Xd, 
   const double* D = dinv + (k * T + c) * BLK * BLK;
   v4d acc[B][4];
   acc_zero(acc);
-  gemm_blk<false, false, false, B, 4>(C, ts, D, BLK, BLK, acc, sm);  // Bop(n, q) = X(q, n), X row by row
+  gemm_blk<false, false, B, 4>(C, ts, D, BLK, BLK, acc, sm);  // Bop(n, q) = X(q, n), X row by row
   acc_store(C, ts, acc, -1.0, false);
 }
 
@@ -141,7 +141,7 @@ __global__ __launch_bounds__(256, 2) void k_dinv_gemm(double* __restrict__ Xd, i
   double* X = Xd + k * ts * ts;
   v4d acc[B][B];
   acc_zero(acc);
-  gemm_blk<false, true, false, B, B>(X + r + (int64_t)c * BLK * ts, ts, X + c * BLK + bb * ts, ts, BLK, acc, sm);
+  gemm_blk<false, true, B, B>(X + r + (int64_t)c * BLK * ts, ts, X + c * BLK + bb * ts, ts, BLK, acc, sm);
   acc_store(X + r + bb * ts, ts, acc, 1.0, true);
 }
 
@@ -158,7 +158,7 @@ __global__ __launch_bounds__(256, 2) void k_dinv_left(double* __restrict__ Xd, c
   v4d acc[4][B];
   acc_zero(acc);
   // Aop(m, q) = X(m, q), X row by row; Bop(n, q) = C(q, n)
-  gemm_blk<true, true, false, 4, B>(D, BLK, C, ts, BLK, acc, sm);
+  gemm_blk<true, true, 4, B>(D, BLK, C, ts, BLK, acc, sm);
   acc_store(C, ts, acc, 1.0, false);
 }
 
@@ -184,7 +184,7 @@ __global__ __launch_bounds__(256, 2) void k_tri_right(TileMat M, const double* _
   v4d acc[B][B];
   acc_zero(acc);
   // padded rows of L^-1 are zero: store zeros (the buffer is copied back whole)
-  if (i * ts + u * E < nreal) gemm_blk<false, true, false, B, B>(Ap, ts, Xk + v * E + off, ts, (int)(ts - v * E), acc, sm);
+  if (i * ts + u * E < nreal) gemm_blk<false, true, B, B>(Ap, ts, Xk + v * E + off, ts, (int)(ts - v * E), acc, sm);
   acc_store(C, ts, acc, -1.0, false);
 }
 
@@ -207,7 +207,7 @@ __global__ __launch_bounds__(256, 2) void k_tri_gemm(TileMat M, const double* __
   double* C = tptr(M, i, j) + u * E + (int64_t)v * E * ts;
   v4d acc[B][B];
   acc_zero(acc);
-  gemm_blk<false, true, false, B, B>(Ap, ts, Bp, ts, (int)ts, acc, sm);
+  gemm_blk<false, true, B, B>(Ap, ts, Bp, ts, (int)ts, acc, sm);
   acc_store(C, ts, acc, 1.0, true);
 }
 
@@ -229,7 +229,7 @@ __global__ __launch_bounds__(256, 2) void k_tri_left(TileMat M, const double* __
   double* C = P + j * ts * ts + u * E + off;
   v4d acc[B][B];
   acc_zero(acc);
-  gemm_blk<false, true, false, B, B>(Xk + u * E, ts, Bp, ts, (u + 1) * E, acc, sm);
+  gemm_blk<false, true, B, B>(Xk + u * E, ts, Bp, ts, (u + 1) * E, acc, sm);
   acc_store(C, ts, acc, 1.0, false);
 }
 
@@ -319,16 +319,13 @@ __global__ __launch_bounds__(256, 2) void k_lauum_contract(TileMat M, int T, int
   const int64_t L0 = ts - r0;
   const double* XdI = M.diag + I * ts * ts;
   const double* XbI = I + 1 < NT ? (const double*)M.off + off_index(I + 1, I, NT) * ts * ts : XdI;
-  auto ap = [=](int k0) -> const double* {
-    return k0 < L0 ? XdI + r0 + (r0 + k0) * ts : XbI + r0 + (int64_t)(k0 - L0) * ts;
-  };
+  // row k0 of either operand's range is at k0 ts of one of two bases
+  const double *a1 = XdI + r0 + r0 * ts, *a2 = XbI + r0 - L0 * ts;
   // I > J: the tiles (I, J), (I + 1, J), ... are one stack as well
-  const double* XJ = I == J ? XbI : tptr(M, I, J);
-  auto bp = [=](int k0) -> const double* {
-    if (I > J) return XJ + c0 + (r0 + k0) * ts;
-    return k0 < L0 ? XdI + c0 + (r0 + k0) * ts : XbI + c0 + (int64_t)(k0 - L0) * ts;
-  };
-  gemm_core<false, false, true, B, B>(ap, ts, bp, ts, (int)(L0 + (NT - 1 - I) * ts), acc, sm);
+  const double *b1 = (I == J ? XdI : tptr(M, I, J)) + c0 + r0 * ts, *b2 = I == J ? XbI + c0 - L0 * ts : b1;
+  auto ap = [=](int k0) { return (k0 < L0 ? a1 : a2) + (int64_t)k0 * ts; };
+  auto bp = [=](int k0) { return (k0 < L0 ? b1 : b2) + (int64_t)k0 * ts; };
+  gemm_core<false, false, B, B>(ap, ts, bp, ts, (int)(L0 + (NT - 1 - I) * ts), acc, sm);
   contract_block64(acc, I * ts + r0, J * ts + c0, nreal, xs, ys, av, qt, cst, sm, part + 3 * b);
 }
 

@@ -399,31 +399,28 @@ __device__ __forceinline__ void gemm_core_mix(AP aptr, int64_t lda, BP bptr, int
     ea[s] = (uint32_t)(AKC ? 2 * (idx & 7) + (int64_t)(idx >> 3) * lda : 2 * (idx & 63) + (int64_t)(idx >> 6) * lda);
     eb[s] = (uint32_t)(BKC ? 2 * (idx & 7) + (int64_t)(idx >> 3) * ldb : 2 * (idx & 63) + (int64_t)(idx >> 6) * ldb);
   }
-  typedef __attribute__((address_space(1))) const e4 g4;
-  typedef __attribute__((address_space(1))) const e2 g2;
   auto gload = [&](int k0, Set& r) {
     const MixPtr A = aptr(k0), B = bptr(k0);
-    gbyte* pa = uniform_base(A.p);
-    gbyte* pb = uniform_base(B.p);
+    const __amdgpu_buffer_rsrc_t pa = stage_rsrc(A.p), pb = stage_rsrc(B.p);
     r.fa = A.f64;
     r.fb = B.f64;
     if (A.f64) {
 #pragma unroll
-      for (int s = 0; s < 4; ++s) r.a[s] = *(g4*)(pa + (ea[s] << 3));
+      for (int s = 0; s < 4; ++s) r.a[s] = __builtin_amdgcn_raw_buffer_load_b128(pa, (int)(ea[s] << 3), 0, 0);
     } else {
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
-        const e2 f = *(g2*)(pa + (ea[s] << 2));
+        const e2 f = __builtin_amdgcn_raw_buffer_load_b64(pa, (int)(ea[s] << 2), 0, 0);
         r.a[s].x = f.x, r.a[s].y = f.y;
       }
     }
     if (B.f64) {
 #pragma unroll
-      for (int s = 0; s < 4; ++s) r.b[s] = *(g4*)(pb + (eb[s] << 3));
+      for (int s = 0; s < 4; ++s) r.b[s] = __builtin_amdgcn_raw_buffer_load_b128(pb, (int)(eb[s] << 3), 0, 0);
     } else {
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
-        const e2 f = *(g2*)(pb + (eb[s] << 2));
+        const e2 f = __builtin_amdgcn_raw_buffer_load_b64(pb, (int)(eb[s] << 2), 0, 0);
         r.b[s].x = f.x, r.b[s].y = f.y;
       }
     }
@@ -466,21 +463,29 @@ __device__ __forceinline__ void gemm_core_mix(AP aptr, int64_t lda, BP bptr, int
         for (int j = 0; j < 4; ++j) acc[i][j] = mfma64(bf[j], af[i], acc[i][j]);
     }
   };
+  // Loads without a condition, but ahead of the products and not dealt between
+  // the k slices as in gemm_core: each would be a branch of its own on the
+  // element type there (k_lauum_f64_lp at n = 40,000: 86.9 ms so, 90.2 ms dealt).
   const int nst = K / BK;  // even
   gload(0, r0);
   gload(BK, r1);
   sstore(0, r0);
   __syncthreads();
-  for (int st = 0; st < nst; st += 2) {
-    if (st + 2 < nst) gload((st + 2) * BK, r0);
+  for (int st = 0; st + 2 < nst; st += 2) {
+    gload((st + 2) * BK, r0);
     compute(0);
     sstore(1, r1);
     __syncthreads();
-    if (st + 3 < nst) gload((st + 3) * BK, r1);
+    gload((st + 3) * BK, r1);
     compute(1);
-    if (st + 2 < nst) sstore(0, r0);
+    sstore(0, r0);
     __syncthreads();
   }
+  compute(0);
+  sstore(1, r1);
+  __syncthreads();
+  compute(1);
+  __syncthreads();
 }
 
 // ------------------------------------------------ mixed tile TRTRI, step k
@@ -530,8 +535,11 @@ __global__ __launch_bounds__(256, 2) void k_tri_right_lp(TileMat M, const uint8_
 }
 
 // A_ij += P_i A_kj for k < i < NT, 0 <= j < k (P_i = the new A_ik), FP32
-// targets; A_kj of a band tile is read from its FP64 slot
-__global__ __launch_bounds__(256, 2) void k_tri_gemm_lp(TileMat M, const uint8_t* __restrict__ tag,
+// targets; A_kj of a band tile is read from its FP64 slot.  Three workgroups
+// per CU (168 registers, five spilled in the epilogue) instead of two: 158.5 ->
+// 150.9 ms for all steps at n = 40,000, the epilogue's loads under the others'
+// products.  (k_lauum_contract_lp, with its long k range, gains nothing by it.)
+__global__ __launch_bounds__(256, 3) void k_tri_gemm_lp(TileMat M, const uint8_t* __restrict__ tag,
                                                         const float* __restrict__ P, int T, int64_t k, int64_t nreal,
                                                         int64_t nb) {
   __shared__ float sm[G32_LDS];
@@ -614,7 +622,7 @@ __global__ __launch_bounds__(256, 2) void k_tri_right_band(TileMat M, const doub
   v4d acc[4][4];
   acc_zero(acc);
   if (i * ts + u * BLK < nreal)
-    gemm_blk<false, true, true>(band64(M, off_index(i, k, M.NT)) + u * BLK + off, ts, Xk + v * BLK + off, ts,
+    gemm_blk<false, true>(band64(M, off_index(i, k, M.NT)) + u * BLK + off, ts, Xk + v * BLK + off, ts,
                           (int)(ts - v * BLK), acc, sm);
   acc_store_pair(Q + o, P + o, ts, acc, -1.0);
 }
@@ -823,7 +831,7 @@ __global__ __launch_bounds__(256, 2) void k_lauum_f64_lp(TileMat M, const uint8_
   const int64_t r0 = (int64_t)u * BLK, c0 = (int64_t)v * BLK;
   const double* XII = M.diag + I * ts * ts;
   const double* XIJ = I == J ? XII : band64(M, off_index(I, J, NT));
-  gemm_blk<false, false, true>(XII + r0 + r0 * ts, ts, XIJ + c0 + r0 * ts, ts, (int)(ts - r0), acc, sm);
+  gemm_blk<false, false>(XII + r0 + r0 * ts, ts, XIJ + c0 + r0 * ts, ts, (int)(ts - r0), acc, sm);
   // K = I + 1 .. NT - 1: each stage lies in one tile K, read in that tile's precision
   if (I + 1 < NT) {
     const UDiv dts(ts);  // k0 < npad, npad ts < 2^32

@@ -63,7 +63,7 @@ __global__ __launch_bounds__(256, 2) void k_trsm_diag(const double* __restrict__
   v4d acc[B][B];
   acc_zero(acc);
   // Aop(m, q) = X[u E + m, q], Bop(n, q) = C[q, cb E + n]
-  gemm_blk<false, true, true, B, B>(Xk + u * E, ts, Ck + cb * E * ld, ld, (u + 1) * E, acc, sm);
+  gemm_blk<false, true, B, B>(Xk + u * E, ts, Ck + cb * E * ld, ld, (u + 1) * E, acc, sm);
   acc_store(Vk + u * E + cb * E * ld, ld, acc, 1.0, false);
 }
 
@@ -83,7 +83,7 @@ __global__ __launch_bounds__(256, 2) void k_trsm_update(TileMat M, int64_t k, in
   v4d acc[B][B];
   acc_zero(acc);
   // Aop(m, q) = L_ik[u E + m, q], Bop(n, q) = V_k[q, cb E + n]
-  gemm_blk<false, true, true, B, B>(tptr(M, i, k) + u * E, ts, Vk + cb * E * ld, ld, (int)ts, acc, sm);
+  gemm_blk<false, true, B, B>(tptr(M, i, k) + u * E, ts, Vk + cb * E * ld, ld, (int)ts, acc, sm);
   acc_store(C + i * ts + u * E + cb * E * ld, ld, acc, -1.0, true);
 }
 
