@@ -321,11 +321,25 @@ __device__ __forceinline__ void gemm_blk(const double* __restrict__ A, int64_t l
 // nb8 = ceil(nb / 8): the blocks resident on one XCD at a time are neighbours
 // in the launch's block order and reuse each other's operand reads in that
 // XCD's L2 (used by the BF16 update, whose blocks are bound by operand reads;
-// the FP64 trailing update ran 3.5% slower with it while it halved the bytes
-// fetched past L2).  The grid must have 8 nb8 workgroups; -1 for the spare ones.
+// the other products, whose order balances blocks of unequal length, take
+// xcd_chunk).  The grid must have 8 nb8 workgroups; -1 for the spare ones.
 __device__ __forceinline__ int64_t xcd_block(int64_t nb) {
   const int64_t nb8 = (nb + 7) / 8;
   const int64_t b = (int64_t)(blockIdx.x % 8) * nb8 + blockIdx.x / 8;
+  return b < nb ? b : -1;
+}
+
+// As xcd_block, in chunks: XCD x takes the chunks x, x + 8, ... of the launch's
+// block order, a chunk being the blocks of one target tile (or one row of
+// them), which share their operands' rows.  The order of the work stays, longest
+// blocks first where they differ.  chunk 1: dispatch order; else the grid is a
+// multiple of 8 chunk, -1 for the spare workgroups.  The rule is xcd_chunk_size.
+__device__ __forceinline__ int64_t xcd_chunk(int64_t nb, int chunk) {
+  int64_t b = blockIdx.x;
+  if (chunk > 1) {
+    const uint32_t q = blockIdx.x / 8, x = blockIdx.x % 8;
+    b = (int64_t)(q / chunk * 8 + x) * chunk + q % chunk;
+  }
   return b < nb ? b : -1;
 }
 

@@ -33,14 +33,14 @@ namespace exg {
 // Block edge 32 B (block_tiles); T = ts / (32 B) blocks per tile edge.
 template <int B>
 __global__ __launch_bounds__(256, 2) void k_chol_update(TileMat M, const double* __restrict__ below, int T, int64_t k,
-                                                        int64_t nreal, int64_t nb, int mode, int64_t off,
+                                                        int64_t nreal, int64_t nb, int chunk, int mode, int64_t off,
                                                         const int32_t* __restrict__ li,
                                                         const int32_t* __restrict__ lj) {
   constexpr int E = 32 * B;
   __shared__ double sm[gemm_lds(B, B)];
   const int64_t ts = M.ts;
-  const int64_t b = blockIdx.x;
-  if (b >= nb) return;
+  const int64_t b = xcd_chunk(nb, chunk);
+  if (b < 0) return;
   const int64_t p = b / (T * T);
   const int sub = (int)(b % (T * T));
   const int u = sub / T, v = sub % T;
@@ -191,12 +191,12 @@ __global__ __launch_bounds__(256, 2) void k_tri_right(TileMat M, const double* _
 // A_ij += P_i A_kj for k < i < NT, 0 <= j < k (P_i = the new A_ik)
 template <int B>
 __global__ __launch_bounds__(256, 2) void k_tri_gemm(TileMat M, const double* __restrict__ P, int T, int64_t k,
-                                                     int64_t nreal, int64_t nb) {
+                                                     int64_t nreal, int64_t nb, int chunk) {
   const int64_t ts = M.ts;
   constexpr int E = 32 * B;
   __shared__ double sm[gemm_lds(B, B)];
-  const int64_t b = blockIdx.x;
-  if (b >= nb) return;
+  const int64_t b = xcd_chunk(nb, chunk);
+  if (b < 0) return;
   const int64_t p = b / (T * T);
   const int sub = (int)(b % (T * T));
   const int u = sub / T, v = sub % T;
@@ -290,12 +290,12 @@ __global__ __launch_bounds__(256, 2) void k_lauum_contract(TileMat M, int T, int
                                                            const double* __restrict__ ys, const double* __restrict__ av,
                                                            const double* __restrict__ qt,
                                                            const double* __restrict__ cst, double* __restrict__ part,
-                                                           int64_t nb) {
+                                                           int64_t nb, int chunk) {
   constexpr int E = 32 * B;
   __shared__ double sm[gemm_lds(B, B)];
   const int64_t ts = M.ts, NT = M.NT;
-  const int64_t b = blockIdx.x;
-  if (b >= nb) return;
+  const int64_t b = xcd_chunk(nb, chunk);
+  if (b < 0) return;
   const int64_t p = b / (T * T);
   const int sub = (int)(b % (T * T));
   const int u = sub / T, v = sub % T;
@@ -336,7 +336,8 @@ static void update_pairs(const TileMat& M, const double* below, int64_t k, int64
   const int B = block_tiles(npairs * T4 * T4);
   const int T = (int)(M.ts / (32 * B));
   const int64_t nblk = npairs * T * T;
-  EXG_BLOCKS(B, k_chol_update, nblk, s, M, below, T, k, nreal, nblk, mode, off, li, lj);
+  const int ch = li ? 1 : xcd_chunk_size(B, T, nblk);
+  EXG_BLOCKS(B, k_chol_update, xcd_chunk_grid(nblk, ch), s, M, below, T, k, nreal, nblk, ch, mode, off, li, lj);
 }
 
 void launch_chol_update(const TileMat& M, const double* below, int64_t k, int64_t nreal, bool diag_only, int part,
@@ -439,7 +440,8 @@ void launch_trtri_rest(const TileMat& M, const double* Xk, double* P, int64_t k,
     const int B = block_tiles(nbelow * k * T4 * T4);
     const int T = (int)(ts / (32 * B));
     const int64_t ng = nbelow * k * T * T;
-    EXG_BLOCKS(B, k_tri_gemm, ng, s, M, P, T, k, nreal, ng);
+    const int ch = xcd_chunk_size(B, T, ng);
+    EXG_BLOCKS(B, k_tri_gemm, xcd_chunk_grid(ng, ch), s, M, P, T, k, nreal, ng, ch);
   }
   if (k > 0) {
     const int B = block_tiles(k * T4 * T4);
@@ -463,7 +465,8 @@ int64_t launch_lauum_contract(const TileMat& M, int64_t nreal, const double* xs,
   const int64_t R = (nreal + BLK - 1) / BLK;
   const int B = block_tiles_uneven(R * (R + 1) / 2);
   const int64_t T = M.ts / (32 * B), nb = M.NT * (M.NT + 1) / 2 * T * T;
-  EXG_BLOCKS(B, k_lauum_contract, nb, s, M, (int)T, nreal, xs, ys, av, qt, cst, part, nb);
+  const int ch = xcd_chunk_size(B, (int)T, nb);
+  EXG_BLOCKS(B, k_lauum_contract, xcd_chunk_grid(nb, ch), s, M, (int)T, nreal, xs, ys, av, qt, cst, part, nb, ch);
   return nb;
 }
 

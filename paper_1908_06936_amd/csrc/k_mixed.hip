@@ -541,11 +541,11 @@ __global__ __launch_bounds__(256, 2) void k_tri_right_lp(TileMat M, const uint8_
 // products.  (k_lauum_contract_lp, with its long k range, gains nothing by it.)
 __global__ __launch_bounds__(256, 3) void k_tri_gemm_lp(TileMat M, const uint8_t* __restrict__ tag,
                                                         const float* __restrict__ P, int T, int64_t k, int64_t nreal,
-                                                        int64_t nb) {
+                                                        int64_t nb, int chunk) {
   __shared__ float sm[G32_LDS];
   const int64_t ts = M.ts, tt = ts * ts;
-  const int64_t b = blockIdx.x;
-  if (b >= nb) return;
+  const int64_t b = xcd_chunk(nb, chunk);
+  if (b < 0) return;
   const int64_t p = b / (T * T);
   const int sub = (int)(b % (T * T));
   const int u = sub / T, v = sub % T;
@@ -968,7 +968,9 @@ void launch_trtri_rest_lp(const TileMat& M, const uint8_t* tag, const double* Xk
   const int64_t nbelow = NT - k - 1;
   if (nbelow > 0 && k > 0) {
     const int64_t ng = nbelow * k * T * T;
-    hipLaunchKernelGGL(k_tri_gemm_lp, dim3((unsigned)ng), dim3(256), 0, s, M, tag, P, T, k, nreal, ng);
+    const int ch = xcd_chunk_size(4, T, ng);
+    hipLaunchKernelGGL(k_tri_gemm_lp, dim3((unsigned)xcd_chunk_grid(ng, ch)), dim3(256), 0, s, M, tag, P, T, k, nreal,
+                       ng, ch);
     const int64_t nbg = bl.cfirst[k] * T * T;  // band tiles of columns < k (those with rows > k are targets)
     if (nbg > 0)
       hipLaunchKernelGGL(k_tri_gemm_band, dim3((unsigned)nbg), dim3(256), 0, s, M, tag, Q, P, bl.li, bl.lj, T, k,

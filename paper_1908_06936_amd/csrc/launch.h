@@ -31,6 +31,30 @@ inline int block_tiles(int64_t nb) {
 // on 64 x 64 blocks.
 inline int block_tiles_uneven(int64_t nb) { return nb >= 1536 ? 4 : (nb >= 64 ? 2 : 1); }
 
+// Blocks per chunk of the XCD order (xcd_chunk) of a launch of nb blocks of one
+// length or longest first, T per tile edge: a whole tile's blocks, one row of
+// them, or 1 (dispatch order), whichever first leaves the fullest XCD (64
+// workgroups at a time) with no more rounds than the dispatch order does.  At
+// n = 40,000 in dispatch order, by rows and by tiles: k_lauum_contract 343, 335
+// and 323 ms, k_tri_gemm 307, 306 and 297 ms, k_chol_update 309, 306 and 303 ms.
+// Only for 128-wide blocks and eight rounds or more (shorter launches of
+// n = 10,000: l 10.05 -> 10.13 ms, (l, grad) 24.2 -> 24.7 ms), and not where
+// whole tiles are skipped or differ (the mixed lists and k_update_lp, whose
+// chunks would load the XCDs unevenly: k_tri_gemm_band 18 -> 25 ms,
+// k_update_lp 88 -> 93 ms).
+inline int xcd_chunk_size(int B, int T, int64_t nb) {
+  if (B != 4 || nb < 4096) return 1;
+  const int64_t plain = ((nb + 7) / 8 + 63) / 64;
+  for (int64_t c = (int64_t)T * T; c > 1; c = c > T ? T : 1) {
+    const int64_t most = ((nb + c - 1) / c + 7) / 8 * c;  // blocks of the fullest XCD
+    if ((most + 63) / 64 <= plain) return (int)c;
+  }
+  return 1;
+}
+inline int64_t xcd_chunk_grid(int64_t nb, int chunk) {
+  return chunk > 1 ? (nb + 8 * chunk - 1) / (8 * chunk) * (8 * chunk) : nb;
+}
+
 // kernel<B> for the block edge 32 B, 256 threads per workgroup
 #define EXG_BLOCKS(tiles, kernel, grid, stream, ...)                                                     \
   do {                                                                                                   \

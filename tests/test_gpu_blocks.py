@@ -124,3 +124,18 @@ def test_dst_ignores_what_lies_outside_the_band(orc, exa, n, band):
     ll_ref, g_ref = orc.loglik_grad_dst(x, y, z, th, 128, band)
     assert ll == pytest.approx(ll_ref, rel=1e-10)
     assert_score_close(g, g_ref, n, th)
+
+
+# block orders over the XCDs: below, at and past the size from which a tile's
+# (or a tile row's) blocks go to one XCD together, against tiles of one block,
+# which are always in dispatch order
+@pytest.mark.parametrize("n,ts", [(11264, 256), (11265, 256), (12000, 512)])
+def test_block_orders_over_the_xcds(exa, n, ts):
+    x, y = inputgen.uniform(n, seed=700 + ts)
+    z = inputgen.smooth_field(x, y, seed=n)
+    th = [1.0, 0.02, 0.5]
+    X, Y, Z = dev(x), dev(y), dev(z)
+    ll, g = exa.Context(ts=ts).loglik_grad(X, Y, Z, th)
+    ll_ref, g_ref = exa.Context(ts=128).loglik_grad(X, Y, Z, th)
+    assert ll == pytest.approx(ll_ref, rel=1e-10)
+    assert_score_close(g, g_ref, n, th)
