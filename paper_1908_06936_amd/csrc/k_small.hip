@@ -272,13 +272,16 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 //   eliminating wave) finish step k - 1's update and waves 4 and 5 write panel
 //   k - 1, scaled, to global memory; between eliminations the eight waves bring
 //   the eight blocks of the next panel up to date.
-// What bounds it is the chain of 128 pivots (broadcast, reciprocal, multiply-adds,
-// the update of the next row: about 260 cycles each) and, in the first steps,
-// the latency of the updates beside it.  The LDS (94 KB) and 128 registers per
-// lane leave room for one trailing-update workgroup on the same CU.  It takes
-// 32 us alone and 47 / 101 us on average in the factorisations of n = 10,000 /
-// 22,500, where a form with one barrier per column (255 in all) took 99 us
-// alone and 123 / 225 us.
+// What bounds it is the chain of 128 pivots (about 200 cycles each: a chain of
+// 98 and the multiply-adds of the rows below) and, in steps 1 to 4, the updates
+// beside it, which only two SIMDs can take: an FP64 MFMA holds up the FP64
+// multiply-adds of its SIMD (4.6 -> 20.7 cycles).  Their blocks come from a table
+// (one scalar load per step), fetched one ahead.  The LDS (95 KB) and 128
+// registers per lane leave room for one trailing-update workgroup on the same
+// CU.  It takes 27 us alone and 49 / 93 us on average in the factorisations of
+// n = 10,000 / 22,500 (the wait for a CU included); with the blocks' indices
+// formed on the way and a branch per row in the elimination's loads 32 us alone
+// (two blocks at a time: 31), with one barrier per column (255 in all) 99 us.
 // Writes L (zeros above the diagonal) over the block, X row by row to dinv
 // (X(r, c) at 128 r + c, the order in which the panels leave LDS), the block's
 // sum of 2 ln L_jj to *ldpart and the first failing global column
@@ -286,10 +289,41 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 // input does not enter the result.
 constexpr int PB = 16;           // step width
 constexpr int PNB = BLK / PB;    // steps
-constexpr int PLD = BLK + PB + 2;  // row panel: 128 columns, then its 16 x 16 diagonal block; the stride keeps
-                                   // reads along its rows and its columns nearly free of bank conflicts
+constexpr int PLD = BLK + PB;  // row panel: 128 columns, then its 16 x 16 diagonal block; 16 columns of two rows
+                               // a stride apart fall into different halves of the banks
 constexpr int PSLOT = PB * PB;
-constexpr int POTRF_LDS = (PNB * (PNB + 1) / 2 * PSLOT + PB * PLD + 6 * PB + BLK) * 8;  // bytes
+constexpr int PSLOTS = PNB * (PNB + 1) / 2;
+constexpr int POTRF_LDS = ((PSLOTS + 1) * PSLOT + PB * PLD + 6 * PB + BLK) * 8;  // bytes
+static_assert(POTRF_LDS + GEMM_LDS * 8 <= 160 * 1024, "one trailing-update workgroup beside it");
+
+// One block update as a scalar: slot, the column blocks of P of the scaled and
+// the plain operand, and whether the slot starts from zero.
+constexpr uint32_t potrf_job(int r, int c, int k) {
+  return (uint32_t)((r * (r + 1) / 2 + c) | (c > k ? c : r) << 6 | (c > k ? r : c) << 9 | (c == k) << 12);
+}
+// The rest of step k - 1: rows r > k, columns c <= r except k, dealt in turn to
+// the four waves that update beside the elimination of panel k; at most seven
+// blocks for one wave, 16 bits each, then their number.
+struct PotrfJobs {
+  uint64_t j[PNB][4][2];
+};
+constexpr PotrfJobs potrf_jobs() {
+  PotrfJobs t{};
+  for (int k = 1; k < PNB; ++k) {
+    int e = 0;
+    for (int r = k + 1; r < PNB; ++r)
+      for (int c = 0; c <= r; ++c)
+        if (c != k) {
+          const int v = e % 4, i = e / 4;
+          t.j[k][v][i / 4] |= (uint64_t)potrf_job(r, c, k - 1) << (16 * (i % 4));
+          t.j[k][v][1] += (uint64_t)1 << 48;
+          ++e;
+        }
+  }
+  return t;
+}
+__constant__ const PotrfJobs POTRF_JOBS = potrf_jobs();
+
 // The LDS is dynamic so that the compiler keeps to 128 registers per lane: two
 // waves per SIMD then fit beside a trailing-update workgroup's two.
 __global__ __launch_bounds__(512, 4) void k_potrf_blk(
@@ -297,7 +331,8 @@ __global__ __launch_bounds__(512, 4) void k_potrf_blk(
     unsigned long long* __restrict__ info, int64_t col0) {
   extern __shared__ double potrf_lds[];
   double* slots = potrf_lds;
-  double* P = slots + PNB * (PNB + 1) / 2 * PSLOT;
+  double* ident = slots + PSLOTS * PSLOT;  // the 16 x 16 identity
+  double* P = ident + PSLOT;
   double* nrd = P + PB * PLD;  // -1 / d_j of the panels k (even, odd; a copy per eliminating wave)
   double* rsc = nrd + 4 * PB;  // 1 / L_jj (a copy per writing wave)
   double* piv = rsc + 2 * PB;  // d_j
@@ -307,40 +342,51 @@ __global__ __launch_bounds__(512, 4) void k_potrf_blk(
   auto slot = [&](int r, int c) { return slots + (r * (r + 1) / 2 + c) * PSLOT; };
   {
     v4d v[5];
-    int r = 0, c = 0, rs[5], cs[5];
+    int r = 0, c = 0;
 #pragma unroll
     for (int s = 0; s < 5; ++s) {
-      const int b = min(8 * s + w, PNB * (PNB + 1) / 2 - 1);  // spare turns repeat the last block
+      const int b = min(8 * s + w, PSLOTS - 1);  // spare turns repeat the last block
       while ((r + 1) * (r + 2) / 2 <= b) ++r;
       c = b - r * (r + 1) / 2;
-      rs[s] = r;
-      cs[s] = c;
       const double* Ab = A + PB * r + (int64_t)(PB * c) * lda;
 #pragma unroll
       for (int q = 0; q < 4; ++q) v[s][q] = Ab[l16 + (4 * q + q16) * lda];
     }
+    if (t < PSLOT) ident[t] = t / PB == t % PB ? 1.0 : 0.0;
 #pragma unroll
     for (int s = 0; s < 5; ++s)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) slot(rs[s], cs[s])[(4 * q + q16) * PB + l16] = v[s][q];
+      for (int q = 0; q < 4; ++q) slots[min(8 * s + w, PSLOTS - 1) * PSLOT + 64 * q + lane] = v[s][q];
   }
-  // step k's update of block (r, c), r > k; T(r, k) starts here, from zero
-  auto upd_load = [&](int r, int c, int k, v4d& acc, v4d& x, v4d& y) {
-    const int cx = c > k ? c : r, cy = c > k ? r : c;
-    const double* S = slot(r, c);
-    const double* nd = nrd + 2 * PB * (k & 1);
+  // the lane's -1 / d_j of panel k
+  auto upd_scale = [&](int k, v4d& nv) {
+    const double* nd = nrd + 2 * PB * (k & 1) + q16;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) nv[q] = nd[4 * q];
+  };
+  // the update of one block (potrf_job); T(r, k) starts in step k, from zero
+  struct Upd {
+    v4d acc, x, y;
+  };
+  auto upd_load = [&](uint32_t job, Upd& u) {
+    const double* S = slots + (job & 63) * PSLOT + lane;
+    const double* pl = P + q16 * PLD + l16;
+    const double *px = pl + (job >> 6 & 7) * PB, *py = pl + (job >> 9 & 7) * PB;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const int row = 4 * q + q16;
-      x[q] = P[row * PLD + PB * cx + l16] * nd[row];
-      y[q] = P[row * PLD + PB * cy + l16];
-      acc[q] = S[row * PB + l16];
+      u.x[q] = px[4 * q * PLD];
+      u.y[q] = py[4 * q * PLD];
+      u.acc[q] = S[64 * q];
     }
   };
-  auto upd_store = [&](int r, int c, const v4d& acc) {
-    double* S = slot(r, c);
+  auto upd_apply = [&](uint32_t job, const v4d& nv, Upd& u) {
+    double* S = slots + (job & 63) * PSLOT + lane;
+    asm volatile("" : "+v"(u.acc));  // loaded in any case: a branch per element costs more
+    if (job >> 12 & 1) u.acc = (v4d){0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int q = 0; q < 4; ++q) S[(4 * q + q16) * PB + l16] = acc[q];
+    for (int q = 0; q < 4; ++q) u.acc = mfma64(u.x[q] * nv[q], u.y[q], u.acc);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) S[64 * q] = u.acc[q];
   };
 #pragma unroll 1
   for (int k = 0;; ++k) {
@@ -350,14 +396,14 @@ __global__ __launch_bounds__(512, 4) void k_potrf_blk(
     if (w < 2) {
       if (k == PNB) break;
       const int col = 64 * w + lane, cb = col >> 4;
-      const double* src = cb > k ? slot(cb, k) : slot(k, cb);
-      const double* dsrc = slot(k, k);
+      const double* src = (cb > k ? slot(cb, k) : cb == k ? ident : slot(k, cb)) + l16;
+      const double* dsrc = slot(k, k) + l16;
       double* nd = nrd + 2 * PB * (k & 1) + PB * w;
       double u[PB], g[PB];  // the lane's panel column, its copy of a diagonal column
 #pragma unroll
       for (int j = 0; j < PB; ++j) {
-        g[j] = dsrc[j * PB + l16];
-        u[j] = cb == k ? (l16 == j ? 1.0 : 0.0) : src[j * PB + l16];
+        g[j] = dsrc[j * PB];
+        u[j] = src[j * PB];
       }
       static_for<0, PB>([&](auto jc) {
         constexpr int j = decltype(jc)::value;
@@ -372,9 +418,15 @@ __global__ __launch_bounds__(512, 4) void k_potrf_blk(
       lds_barrier();  // nobody reads panel k - 1 any more
 #pragma unroll
       for (int j = 0; j < PB; ++j) P[j * PLD + col] = u[j];
-      if (col < PB) {
+      if (lane < PB) {  // half of the diagonal block's rows each
+        double* Pd = P + BLK + lane;
+        if (w == 0) {
 #pragma unroll
-        for (int j = 0; j < PB; ++j) P[j * PLD + BLK + col] = g[j];
+          for (int j = 0; j < PB / 2; ++j) Pd[j * PLD] = g[j];
+        } else {
+#pragma unroll
+          for (int j = PB / 2; j < PB; ++j) Pd[j * PLD] = g[j];
+        }
       }
     } else if (w == 4 || w == 5) {
       if (k > 0) {  // panel k - 1 to global memory
@@ -386,14 +438,17 @@ __global__ __launch_bounds__(512, 4) void k_potrf_blk(
         double* Ak = A + PB * (k - 1) * lda + col;
         double* X = dinv + PB * (k - 1) * BLK + col;
         // L takes its diagonal block's columns from the panel's tail
-        const double* Pc = P + (cb == k - 1 ? BLK + l16 : col);
+        const double *Pc = P + (cb == k - 1 ? BLK + l16 : col), *Px = P + col;
 #pragma unroll
         for (int j = 0; j < PB; ++j) {
-          const double rj = rs[j], v = Pc[j * PLD] * rj, x = P[j * PLD + col] * rj;
-          Ak[(uint32_t)j * (uint32_t)lda] = d > j ? v : (d == j ? sd : 0.0);
+          const double rj = rs[j];
+          double v = Pc[j * PLD] * rj, x = Px[j * PLD] * rj;
+          asm volatile("" : "+v"(v), "+v"(x));  // selected, not branched over
+          Ak[(uint32_t)j * (uint32_t)lda] = d > j ? v : 0.0;
           X[j * BLK] = cb < k ? x : 0.0;
         }
         if (cb == k - 1) {
+          Ak[(uint32_t)l16 * (uint32_t)lda] = sd;
           piv[col] = pv;
           if (!(pv > 0.0) || !(pv <= DBL_MAX)) atomicMin(info, (unsigned long long)(col0 + col + 1));
         }
@@ -402,47 +457,47 @@ __global__ __launch_bounds__(512, 4) void k_potrf_blk(
       lds_barrier();
     } else {
       if (k == PNB) break;
-      // the rest of step k - 1: rows r > k, columns c <= r except k (r of them),
-      // dealt to the four waves in turn and taken two at a time
-      int r = k + 1, e = (w & 1) + 2 * (w >> 2);
-      auto next = [&](int* rr, int* cc) {
-        while (e >= r && r < PNB) e -= r++;
-        *rr = r;
-        *cc = e + (e >= k);
-        e += 4;
-        return r < PNB;
-      };
-      int r0, c0, r1, c1;
+      // the wave's share of the rest of step k - 1; each block's operands are read
+      // while the products of the one before run
+      const int v = (w & 1) + 2 * (w >> 2);
+      uint64_t j0 = POTRF_JOBS.j[k][v][0], j1 = POTRF_JOBS.j[k][v][1];
+      int left = (int)(j1 >> 48);
+      if (left > 0) {
+        auto next = [&]() {
+          const uint32_t job = (uint32_t)j0 & 0xffff;
+          j0 = j0 >> 16 | j1 << 48;
+          j1 >>= 16;
+          return job;
+        };
+        v4d nv;
+        Upd a, b;
+        upd_scale(k - 1, nv);
+        uint32_t ja = next(), jb;
+        upd_load(ja, a);
 #pragma unroll 1
-      while (k > 0 && next(&r0, &c0)) {
-        const bool two = next(&r1, &c1);
-        if (!two) r1 = r0, c1 = c0;
-        v4d a0, x0, y0, a1, x1, y1;
-        upd_load(r0, c0, k - 1, a0, x0, y0);
-        upd_load(r1, c1, k - 1, a1, x1, y1);
-        asm volatile("" : "+v"(a0), "+v"(a1));  // loaded in any case: a branch per element costs more
-        if (c0 == k - 1) a0 = (v4d){0.0, 0.0, 0.0, 0.0};
-        if (c1 == k - 1) a1 = (v4d){0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          a0 = mfma64(x0[q], y0[q], a0);
-          a1 = mfma64(x1[q], y1[q], a1);
+        for (;;) {
+          jb = left > 1 ? next() : ja;  // the last one's reads are not used
+          upd_load(jb, b);
+          upd_apply(ja, nv, a);
+          if (--left == 0) break;
+          ja = left > 1 ? next() : jb;
+          upd_load(ja, a);
+          upd_apply(jb, nv, b);
+          if (--left == 0) break;
         }
-        upd_store(r0, c0, a0);
-        if (two) upd_store(r1, c1, a1);
       }
       lds_barrier();
     }
+    // the blocks of panel k + 1, one per wave
+    const int r = w <= k + 1 ? k + 1 : w, c = w <= k + 1 ? w : k + 1;
+    const uint32_t job = potrf_job(r, c, k);
     lds_barrier();  // panel k eliminated
-    if (k < PNB - 1) {  // the blocks of panel k + 1, one per wave
-      const int r = w <= k + 1 ? k + 1 : w, c = w <= k + 1 ? w : k + 1;
-      v4d a, x, y;
-      upd_load(r, c, k, a, x, y);
-      asm volatile("" : "+v"(a));
-      if (c == k) a = (v4d){0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-      for (int q = 0; q < 4; ++q) a = mfma64(x[q], y[q], a);
-      upd_store(r, c, a);
+    if (k < PNB - 1) {
+      v4d nv;
+      Upd a;
+      upd_load(job, a);
+      upd_scale(k, nv);
+      upd_apply(job, nv, a);
     }
   }
   // 2 sum ln L_jj = sum ln d_j, in a fixed order
