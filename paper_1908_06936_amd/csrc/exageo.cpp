@@ -108,7 +108,7 @@ Plan make_plan(int64_t n, int64_t ts, int want_grad, int precision = EXAGEO_FP64
   p.off_keys = take((size_t)p.P * 8);
   p.off_box = take(8 * 8);
   p.off_qt = take((size_t)exg::quad_table_doubles() * 8);
-  p.off_cst = take(8 * 8);
+  p.off_cst = take(16 * 8);
   p.off_part = take((size_t)(p.grad ? exg::lauum_blocks(ts, p.NT) + p.pool_cap * p.T * p.T : 1) * 3 * 8);
   p.off_out = take(16 * 8);
   p.off_info = take(8);

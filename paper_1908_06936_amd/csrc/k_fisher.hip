@@ -48,6 +48,9 @@ __global__ __launch_bounds__(256) void k_gen_dstrip(double* __restrict__ S, int 
   const int u = sub / T, v = sub % T;
   const int64_t jj = tile / NT, K = tile % NT;
   if (jj >= W || J0 + jj >= NT) return;
+  __shared__ __attribute__((aligned(16))) double tab[(COMP + 1) * CH_TAB];
+  stage_tables<COMP + 1>(qt, tab);
+  __syncthreads();
   const int r = threadIdx.x & 127, c0 = threadIdx.x >> 7;
   const int64_t gi = (J0 + jj) * ts + u * BLK + r;
   double* out = S + (jj * NT + K) * ts * ts + u * BLK + r + (int64_t)v * BLK * ts;
@@ -58,7 +61,7 @@ __global__ __launch_bounds__(256) void k_gen_dstrip(double* __restrict__ S, int 
     double val = 0.0;
     if (!ipad && gj < nreal) {
       double d0, d1, d2;
-      matern_grad(loc_dist(xi, yi, xs[gj], ys[gj], cst), cst, qt, &d0, &d1, &d2);
+      matern_grad(loc_dist(xi, yi, xs[gj], ys[gj], cst), cst, qt, tab, &d0, &d1, &d2);
       val = COMP == 0 ? d0 : (COMP == 1 ? d1 : d2);
     }
     out[(int64_t)c * ts] = val;

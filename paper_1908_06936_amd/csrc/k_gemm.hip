@@ -292,7 +292,8 @@ __global__ __launch_bounds__(256, 2) void k_lauum_contract(TileMat M, int T, int
                                                            const double* __restrict__ cst, double* __restrict__ part,
                                                            int64_t nb, int chunk) {
   constexpr int E = 32 * B;
-  __shared__ double sm[gemm_lds(B, B)];
+  constexpr int LDS = gemm_lds(B, B) > contract_lds(B) ? gemm_lds(B, B) : contract_lds(B);
+  __shared__ __attribute__((aligned(16))) double sm[LDS];
   const int64_t ts = M.ts, NT = M.NT;
   const int64_t b = xcd_chunk(nb, chunk);
   if (b < 0) return;

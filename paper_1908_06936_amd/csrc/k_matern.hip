@@ -47,15 +47,29 @@ __global__ void k_quad_table(double s2, double beta, double nu, double metric, d
     cst[C_S2C] = s2 * c;
     cst[C_METRIC] = metric;
     cst[C_NUG] = nugget;
+    cst[C_RBETA] = 1.0 / beta;
     if (info) *info = ~0ull;
   }
 }
 
+// CH_POW.t[n][k]: the coefficient of t^k in the Chebyshev polynomial T_n
+struct ChebPowers {
+  int t[CH_N][CH_N];
+};
+constexpr ChebPowers cheb_powers() {
+  ChebPowers p{};
+  p.t[0][0] = p.t[1][1] = 1;
+  for (int n = 2; n < CH_N; ++n)
+    for (int k = 0; k <= n; ++k) p.t[n][k] = (k > 0 ? 2 * p.t[n - 1][k - 1] : 0) - p.t[n - 2][k];
+  return p;
+}
+__constant__ const ChebPowers CH_POW = cheb_powers();
+
 // Tables of u0, u1, u2 on segment blockIdx.x of ln x (see matern_dev.h): the
 // functions at the 13 Chebyshev points by the quadrature; stored per function
-// are its value at the segment centre (the middle point, t = 0) and the
-// Chebyshev coefficients of ln(u / u_centre), c_k = (2/N) sum_j d_j
-// cos(pi k (j + 1/2) / N), whose magnitudes stay small.  Runs after
+// are factors with its value at the segment centre (the middle point, t = 0) and
+// the coefficients of ln(u / u_centre) in powers of t, from the Chebyshev
+// coefficients c_k = (2/N) sum_j d_j cos(pi k (j + 1/2) / N).  Runs after
 // k_quad_table.  Bound by latency: 16 lanes share the exponentials of the up to
 // 400 nodes of one point, one thread per function then adds them in node order
 // (so the table does not depend on the split), and the logarithms and cosines
@@ -63,7 +77,7 @@ __global__ void k_quad_table(double s2, double beta, double nu, double metric, d
 // coefficient: 68 us.
 __global__ __launch_bounds__(256) void k_cheb_table(double* __restrict__ qt, const double* __restrict__ cst) {
   constexpr int LP = 16;  // lanes per point
-  __shared__ double fv[3][CH_N], lg[3][CH_N], cs[CH_N][CH_N], ex[CH_N][QNK + 1], xs[CH_N];
+  __shared__ double fv[3][CH_N], lg[3][CH_N], ch[3][CH_N], cs[CH_N][CH_N], ex[CH_N][QNK + 1], xs[CH_N];
   __shared__ int nk[CH_N];
   const int seg = blockIdx.x, t = threadIdx.x;
   const double pi = 3.14159265358979323846;
@@ -103,16 +117,25 @@ __global__ __launch_bounds__(256) void k_cheb_table(double* __restrict__ qt, con
   __syncthreads();
   if (t < 3 * CH_N) lg[t / CH_N][t % CH_N] = log(fv[t / CH_N][t % CH_N] / fv[t / CH_N][CH_MID]);
   __syncthreads();
+  if (t < 3 * CH_N) {
+    const int f = t / CH_N, k = t % CH_N;
+    double c = 0.0;
+    for (int q = 0; q < CH_N; ++q) c += lg[f][q] * cs[k][q];
+    ch[f][k] = c * (2.0 / CH_N);
+  }
+  __syncthreads();
   if (t < 3 * 16) {
     const int f = t >> 4, k = t & 15;
+    const double A = cst[C_S2C] * fv[f][CH_MID];
     double c = 0.0;
-    if (k < CH_N) {
-      for (int q = 0; q < CH_N; ++q) c += lg[f][q] * cs[k][q];
-      c *= 2.0 / CH_N;
-    } else if (k == CH_N) {
-      c = fv[f][CH_MID];
+    if (k < CH_A) {  // coefficient of t^(k + 1), the small terms first
+      for (int q = CH_N - 1; q > k; --q) c = fma((double)CH_POW.t[q][k + 1], ch[f][q], c);
+    } else if (k == CH_A) {
+      c = f == 1 ? A / cst[C_BETA] : A;
+    } else if (k == CH_A + 1) {
+      c = cst[C_C] * fv[f][CH_MID];
     }
-    qt[QT_CHEB_OFF + seg * CH_STRIDE + f * 16 + k] = c;
+    if (k < CH_STRIDE) qt[QT_CHEB_OFF + f * CH_TAB + seg * CH_STRIDE + k] = c;
   }
 }
 
@@ -147,6 +170,9 @@ __global__ __launch_bounds__(256) void k_gen_tiles(TileMat M, int T, int64_t nre
   if (I == J && u < v) return;
   const bool zero_tile = M.dst > 0 && I - J >= M.dst;  // outside the DST band
   if (zero_tile && !fill_zero) return;
+  __shared__ __attribute__((aligned(16))) double tab[CH_TAB];
+  stage_tables<1>(qt, tab);
+  __syncthreads();
   const int r = threadIdx.x & 127, c0 = part * ncol + (threadIdx.x >> 7);
   const int64_t gi = I * ts + u * BLK + r;
   const bool ipad = gi >= nreal;
@@ -174,7 +200,7 @@ __global__ __launch_bounds__(256) void k_gen_tiles(TileMat M, int T, int64_t nre
     } else if (ipad || gj >= nreal) {
       val = (gi == gj) ? 1.0 : 0.0;
     } else {
-      val = matern_value(loc_dist(xi, yi, xs[gj], ys[gj], cst), cst, qt);
+      val = matern_value(loc_dist(xi, yi, xs[gj], ys[gj], cst), cst, qt, tab);
       if (gi == gj) val += cst[C_NUG];  // the observation's own noise
     }
     const int64_t e = (int64_t)c * ts;
@@ -192,7 +218,7 @@ __global__ __launch_bounds__(256) void k_gen_dense(double* __restrict__ cov, int
   if (i >= n) return;
   const double xi = x[i], yi = y[i];
   for (int64_t j = blockIdx.y; j < n; j += gridDim.y) {
-    cov[i + j * ldc] = matern_value(loc_dist(xi, yi, x[j], y[j], cst), cst, qt) + (i == j ? cst[C_NUG] : 0.0);
+    cov[i + j * ldc] = matern_value(loc_dist(xi, yi, x[j], y[j], cst), cst, qt, qt + QT_CHEB_OFF) + (i == j ? cst[C_NUG] : 0.0);
   }
 }
 
@@ -231,16 +257,19 @@ __global__ __launch_bounds__(256) void k_sigma_residual(const double* __restrict
                                                         int64_t nreal, int64_t npad, const double* __restrict__ qt,
                                                         const double* __restrict__ cst, double* __restrict__ r) {
   __shared__ double red[256];
+  __shared__ __attribute__((aligned(16))) double tab[CH_TAB];
   const int64_t i = blockIdx.x;
   if (i >= npad) return;
   if (i >= nreal) {
     if (threadIdx.x == 0) r[i] = 0.0;
     return;
   }
+  stage_tables<1>(qt, tab);
+  __syncthreads();
   const double px = xs[i], py = ys[i];
   double s = 0.0;
   for (int64_t j = threadIdx.x; j < nreal; j += 256)
-    s += matern_value(loc_dist(px, py, xs[j], ys[j], cst), cst, qt) * av[j];
+    s += matern_value(loc_dist(px, py, xs[j], ys[j], cst), cst, qt, tab) * av[j];
   double v[1] = {s};
   block_sum<1>(v, red);
   if (threadIdx.x == 0) r[i] = zs[i] - (v[0] + cst[C_NUG] * av[i]);

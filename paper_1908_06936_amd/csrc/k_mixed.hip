@@ -166,7 +166,7 @@ __global__ __launch_bounds__(256) void k_tile_corr(const double* __restrict__ dm
                                                    double* __restrict__ corr) {
   const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (q >= noff) return;
-  corr[q] = matern_value(dmin[q], cst, qt) / cst[C_S2];
+  corr[q] = matern_value(dmin[q], cst, qt, qt + QT_CHEB_OFF) / cst[C_S2];
 }
 
 // --------------------------------------------------------- panel staging
@@ -769,7 +769,7 @@ __global__ __launch_bounds__(256, 2) void k_lauum_contract_lp(TileMat M, const u
                                                               const double* __restrict__ qt,
                                                               const double* __restrict__ cst,
                                                               double* __restrict__ part, int64_t nb) {
-  __shared__ float sm[G32_LDS];
+  __shared__ __attribute__((aligned(16))) float sm[G32_LDS > CONTRACT_LDS32 ? G32_LDS : CONTRACT_LDS32];
   const int64_t ts = M.ts, NT = M.NT;
   const int64_t b = blockIdx.x;
   if (b >= nb) return;

@@ -20,12 +20,15 @@ __global__ __launch_bounds__(256) void k_krige_mean(const double* __restrict__ x
                                                     int64_t m, const double* __restrict__ qt,
                                                     const double* __restrict__ cst, double* __restrict__ mean) {
   __shared__ double red[256];
+  __shared__ __attribute__((aligned(16))) double tab[CH_TAB];
   const int64_t i = blockIdx.x;
   if (i >= m) return;
+  stage_tables<1>(qt, tab);
+  __syncthreads();
   const double px = xn[i], py = yn[i];
   double s = 0.0;
   for (int64_t j = threadIdx.x; j < nreal; j += 256) {
-    s += matern_value(loc_dist(px, py, xs[j], ys[j], cst), cst, qt) * av[j];
+    s += matern_value(loc_dist(px, py, xs[j], ys[j], cst), cst, qt, tab) * av[j];
   }
   double v[1] = {s};
   block_sum<1>(v, red);
@@ -45,7 +48,7 @@ __global__ __launch_bounds__(256) void k_gen_cross(const double* __restrict__ xs
   if (j >= npad || c >= ncols) return;
   double v = 0.0;
   if (j < nreal && c0 + c < m) {
-    v = matern_value(loc_dist(xs[j], ys[j], xn[c0 + c], yn[c0 + c], cst), cst, qt);
+    v = matern_value(loc_dist(xs[j], ys[j], xn[c0 + c], yn[c0 + c], cst), cst, qt, qt + QT_CHEB_OFF);
   }
   C[j + c * ldc] = v;
 }

@@ -139,3 +139,28 @@ def test_block_orders_over_the_xcds(exa, n, ts):
     ll_ref, g_ref = exa.Context(ts=128).loglik_grad(X, Y, Z, th)
     assert ll == pytest.approx(ll_ref, rel=1e-10)
     assert_score_close(g, g_ref, n, th)
+
+
+# entries at the ends of the table and of the fast forms: distances below and
+# above e^-23 beta and 700 beta, zero, squares that overflow and nearly vanish,
+# and ranges outside the short division, against the closed forms of nu = 1/2
+# and 3/2 in extended precision
+@pytest.mark.parametrize("beta", [1.0, 0.3, 3.0, 1e-120, 1e120])
+@pytest.mark.parametrize("nu", [0.5, 1.5])
+def test_matern_entries_at_the_ends(exa, nu, beta):
+    ld = np.longdouble
+    x = np.concatenate([
+        np.exp(-23.0) * np.array([1e-3, 0.5, 1.0 - 1e-9, 1.0, 1.0 + 1e-9, 2.0]),
+        np.array([1e-6, 1e-3, 0.25, np.sqrt(0.5), 1.0, np.sqrt(2.0), 2.0, 9.0, 100.0, 699.0, 699.999]),
+        np.exp(-23.0 + 0.25 * np.array([1, 17, 60, 92, 93, 118])) * (1 + 1e-13)])
+    r = np.concatenate([[0.0], x * beta, [701.0 * beta, 1e8 * beta]])
+    if beta == 1.0:
+        r = np.concatenate([r, [1e160]])
+    cov = exa.Context(ts=128).matern_cov(dev(r), dev(np.zeros_like(r)), [1.7, beta, nu]).cpu().numpy()
+    got = cov[0]
+    q = r.astype(ld) / ld(beta)
+    ref = ld(1.7) * np.exp(-q) * (1 if nu == 0.5 else 1 + q)
+    ref[q > 700] = 0
+    assert got[0] == 1.7 and np.all(got[q > 700] == 0)
+    assert np.all(np.abs(got - ref) <= 1e-14 * ref)
+    np.testing.assert_array_equal(cov, cov.T)
