@@ -1104,7 +1104,8 @@ exageo_status exageo_simulate(exageo_ctx* c, int64_t n, const double* x, const d
   st = factorize(c, p, theta, false);
   if (st) return st;
   double* w = at<double>(c, p.off_tmp);
-  exg::launch_trmv_lower(tilemat(c, p), p.n, at<double>(c, p.off_zs), w, c->stream);
+  // (the 128-block inverses, npad x 128, have served the factorisation)
+  exg::launch_trmv_lower(tilemat(c, p), p.n, at<double>(c, p.off_zs), at<double>(c, p.off_dinv), w, c->stream);
   exg::launch_scatter(w, at<int32_t>(c, p.off_perm), p.n, z, c->stream);
   HIPCHK(c, hipGetLastError());
   double out[6], box[5];

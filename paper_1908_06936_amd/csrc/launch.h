@@ -97,7 +97,9 @@ void launch_solve_below(const TileMat& M, int64_t k, int64_t nreal, const double
 void launch_solve_below_lp(const TileMat& M, const uint8_t* tag, int64_t k, int64_t nreal, const double* y,
                            double* rhs, hipStream_t s);
 void launch_trsv_bwd(const TileMat& M, const double* Xd, double* rhs, double* a, hipStream_t s);
-void launch_trmv_lower(const TileMat& M, int64_t nreal, const double* e, double* w, hipStream_t s);
+// w = L e; part: scratch of TRMV_PARTS vectors of the padded length
+constexpr int64_t TRMV_PARTS = 32;
+void launch_trmv_lower(const TileMat& M, int64_t nreal, const double* e, double* part, double* w, hipStream_t s);
 // out[0..2] = l, log det, quadratic form; out[OUT_INFO], out[OUT_BOX ..] the
 // first failed pivot (as an integer) and box[0..4]
 enum { OUT_INFO = 6, OUT_BOX = 7, OUT_COUNT = 12 };

@@ -164,3 +164,18 @@ def test_matern_entries_at_the_ends(exa, nu, beta):
     assert got[0] == 1.7 and np.all(got[q > 700] == 0)
     assert np.all(np.abs(got - ref) <= 1e-14 * ref)
     np.testing.assert_array_equal(cov, cov.T)
+
+
+# z = L e by row blocks and shares of the tile columns: one tile, as many tiles as
+# shares, more tiles than shares and a last block with one row
+@pytest.mark.parametrize("n,ts", [(1, 128), (100, 256), (700, 128), (1025, 128), (4225, 128), (2049, 1024)])
+def test_simulate_shares(orc, exa, n, ts):
+    x, y = inputgen.uniform(n, seed=800 + n)
+    th = [1.2, 0.05, 0.5]
+    e = inputgen.normals(n, seed=n)
+    z = exa.Context(ts=ts).simulate(dev(x), dev(y), th, dev(e)).cpu().numpy()
+    # L is the factor in the library's order of the locations: z^T Sigma^-1 z =
+    # e^T e whatever that order is, and every tile size has the same one
+    assert z @ np.linalg.solve(orc.matern_cov(x, y, th), z) == pytest.approx(e @ e, rel=1e-9)
+    other = exa.Context(ts=384).simulate(dev(x), dev(y), th, dev(e)).cpu().numpy()
+    np.testing.assert_allclose(z, other, rtol=0, atol=1e-9 * np.abs(e).max())
