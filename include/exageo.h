@@ -31,11 +31,12 @@
  *   outputs    host memory unless stated otherwise.
  *   streams    all work is queued on the stream given to exageo_create; a call
  *              returns after synchronising that stream only when it has to
- *              hand host scalars back.  Inside a call a second stream of the
- *              context (default priority) runs the next panel of the
- *              factorisation and half of each step of the inverse factor,
- *              ordered against the caller's stream by events; it is idle
- *              whenever a call returns.
+ *              hand host scalars back.  Inside a call two more streams of the
+ *              context (default priority) run the next panel of the
+ *              factorisation and half of each step of the inverse factor, and
+ *              the forward solve of the tiles whose panels are done, ordered
+ *              against the caller's stream by events; both are idle whenever a
+ *              call returns.
  *   order      results do not depend on the order of the locations: the
  *              library sorts a private copy along a Morton (Z-order) curve.
  *   errors     no C++ exception crosses the ABI; every call returns a status.

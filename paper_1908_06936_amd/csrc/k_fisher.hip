@@ -36,7 +36,8 @@ __device__ __forceinline__ double* low_tile(double* B, int64_t I, int64_t J, int
 // tile J0 + jj, columns those of tile K, at (jj NT + K) ts^2; zero on padding
 // One kernel per parameter, so that only its own interpolation table is read
 // and evaluated (matern_grad inlines; 162 us a launch at n = 6,400 for either
-// parameter, 86 us now for beta and 123 us for nu).
+// parameter when one kernel took both, 86 us for beta and 123 us for nu with the
+// tables in global memory, 60 and 72 us with them in LDS).
 template <int COMP>
 __global__ __launch_bounds__(256) void k_gen_dstrip(double* __restrict__ S, int T, int64_t NT, int64_t ts,
                                                     int64_t J0, int64_t W, int64_t nreal,

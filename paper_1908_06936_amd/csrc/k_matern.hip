@@ -153,7 +153,9 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
 // each rounded to nearest even from the FP64 value, or FP64 in the band pool
 // (tag 2).  A block's columns are shared by `parts` workgroups: 1 where the
 // blocks fill the chip, 8 where they would not (n = 400, 16 real blocks: 73 us
-// with 64 entries one after another in each thread, 14 us with 8).  Tiles
+// with 64 entries one after another in each thread, 11 us with 8).  Bound by the
+// entries' instructions and table reads (matern_dev.h): n = 40,000 in 6.0 ms,
+// 1.3e11 entries/s and 1.1 TB/s written.  Tiles
 // outside the DST band are zero and are written only if fill_zero.
 __global__ __launch_bounds__(256) void k_gen_tiles(TileMat M, int T, int64_t nreal, const double* __restrict__ xs,
                                                    const double* __restrict__ ys, const double* __restrict__ qt,
@@ -251,7 +253,9 @@ void launch_gen_tiles(const TileMat& M, int64_t nreal, const double* xs, const d
 // r_i = z_i - sum_j Sigma_ij a_j over the real points (Sigma regenerated in
 // FP64, the nugget on the diagonal), r_i = 0 on padded rows; one 256-thread
 // workgroup per row, fixed-order reduction.  The residual of a solve done
-// through a lower-precision factor.
+// through a lower-precision factor.  Bound by the entries, as k_gen_tiles:
+// n = 40,000 in 7.0 ms, 2.3e11 entries/s (12.1 ms with the table in global memory
+// and the library's functions).
 __global__ __launch_bounds__(256) void k_sigma_residual(const double* __restrict__ xs, const double* __restrict__ ys,
                                                         const double* __restrict__ zs, const double* __restrict__ av,
                                                         int64_t nreal, int64_t npad, const double* __restrict__ qt,

@@ -520,8 +520,10 @@ __global__ __launch_bounds__(256) void k_pad_blk(double* __restrict__ dinv, doub
 // Forward substitution on one diagonal tile, y = L_kk^-1 rhs, by the 128-blocks
 // and their inverses (nblk blocks with real rows; y = 0 on the others): one
 // workgroup, bound by what one CU reads (128 KB a block, most of it written on
-// other XCDs).  Fetching ahead and X's lower half only: 32 us for
-// six blocks, 45 where the chip is busy, 37 and 73 without.
+// other XCDs): 21 us for four blocks, 36 for six (23 and 37 with the zero half of
+// the inverses read too).  58 registers, so that it fits on a CU beside a
+// trailing-update workgroup; fetching the next block ahead took 96, 32 us alone,
+// and waited 2 ms a tile for a free CU at n = 40,000.
 __global__ __launch_bounds__(1024) void k_tile_fwd(const double* __restrict__ L, int64_t ts,
                                                    const double* __restrict__ dinv, const double* __restrict__ rhs,
                                                    double* __restrict__ y, int nblk) {
@@ -530,33 +532,17 @@ __global__ __launch_bounds__(1024) void k_tile_fwd(const double* __restrict__ L,
   double* red = sb + BLK;
   const int t = threadIdx.x, r = t & 127, h = t >> 7;
   for (int q = t; q < ts; q += 1024) fy[q] = 0.0;
-  // 16 elements per thread of block (c, k), k < c, of L, or of X_c (k = c: row
-  // t / 8), the next block's fetched while this one is used
-  // (X_c is lower triangular: row 8 rb + . ends in column group rb)
-  const int row = t >> 3, l = t & 7, rb = __builtin_amdgcn_readfirstlane(t >> 6);
-  double v[16], nx[16];
-  auto fetch = [&](int c, int k) {
-    const bool lt = k < c;
-    const double* p = lt ? L + c * BLK + r + (int64_t)(k * BLK + h) * ts : dinv + ((int64_t)c * BLK + row) * BLK + l;
-    const int64_t step = lt ? 8 * ts : 8;
-#pragma unroll
-    for (int e = 0; e < 16; ++e) nx[e] = lt || e <= rb ? p[e * step] : 0.0;
-  };
-  auto take = [&]() {
-#pragma unroll
-    for (int e = 0; e < 16; ++e) v[e] = nx[e];
-  };
-  fetch(0, 0);
-  take();
   __syncthreads();
   for (int c = 0; c < nblk; ++c) {
+    const double* Lr = L + c * BLK + r;
     double s = 0.0;
-    const double rc = t < BLK ? rhs[c * BLK + t] : 0.0;
-    for (int k = 0; k < c; ++k) {
-      fetch(c, k + 1);
+    int q = h;
+    for (; q < c * BLK; q += 128) {  // 16 loads in flight per thread
+      double v[16];
 #pragma unroll
-      for (int e = 0; e < 16; ++e) s += v[e] * fy[k * BLK + h + 8 * e];
-      take();
+      for (int e = 0; e < 16; ++e) v[e] = Lr[(int64_t)(q + 8 * e) * ts];
+#pragma unroll
+      for (int e = 0; e < 16; ++e) s += v[e] * fy[q + 8 * e];
     }
     red[t] = s;
     __syncthreads();
@@ -564,21 +550,22 @@ __global__ __launch_bounds__(1024) void k_tile_fwd(const double* __restrict__ L,
       double a = 0.0;
 #pragma unroll
       for (int g = 0; g < 8; ++g) a += red[g * BLK + t];
-      sb[t] = rc - a;
+      sb[t] = rhs[c * BLK + t] - a;
     }
-    if (c + 1 < nblk) fetch(c + 1, 0);
     __syncthreads();
     // y_c = X s, X row by row: eight lanes per row
     {
+      const int row = t >> 3, l = t & 7, rb = __builtin_amdgcn_readfirstlane(t >> 6);  // X is lower triangular
+      const double* X = dinv + ((int64_t)c * BLK + row) * BLK;
       double a = 0.0;
 #pragma unroll
-      for (int e = 0; e < 16; ++e) a += v[e] * sb[8 * e + l];
+      for (int e = 0; e < 16; ++e)
+        if (e <= rb) a += X[8 * e + l] * sb[8 * e + l];
       a += __shfl_xor(a, 4, 8);
       a += __shfl_xor(a, 2, 8);
       a += __shfl_xor(a, 1, 8);
       if (l == 0) fy[c * BLK + row] = a;
     }
-    if (c + 1 < nblk) take();
     __syncthreads();
   }
   for (int q = t; q < ts; q += 1024) y[q] = fy[q];
