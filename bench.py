@@ -31,12 +31,13 @@ HBM_PEAK_GBS = 8000.0
 # passes over this workload (profiles/k_chol_update_n40000_ts768_counters.md):
 # FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0, the factors that make a plain 1 GiB
 # device copy read and write 1 GiB.  Valid only for the kernel source the
-# counters were taken on: the shared GEMM core (common.h) and the text of
-# k_chol_update and of its launcher (fingerprint below); otherwise null.
-TRAFFIC_BYTES_PER_LAUNCH = (4.9837e6 * 2.0 + 1.0333e6 * 1.0) * 1024
-TRAFFIC_FILES = ("paper_1908_06936_amd/csrc/common.h",)
-TRAFFIC_FUNCTIONS = ("paper_1908_06936_amd/csrc/k_gemm.hip", ("k_chol_update", "launch_chol_update"))
-TRAFFIC_FINGERPRINT = "75b22615e038699458018ddce2e921c3b65fd274"
+# counters were taken on: the shared GEMM core (common.h), the launch rules
+# (launch.h) and the text of k_chol_update and of its launchers (fingerprint
+# below); otherwise null.
+TRAFFIC_BYTES_PER_LAUNCH = (2.9442e6 * 2.0 + 1.0331e6 * 1.0) * 1024
+TRAFFIC_FILES = ("paper_1908_06936_amd/csrc/common.h", "paper_1908_06936_amd/csrc/launch.h")
+TRAFFIC_FUNCTIONS = ("paper_1908_06936_amd/csrc/k_gemm.hip", ("k_chol_update", "update_pairs", "launch_chol_update"))
+TRAFFIC_FINGERPRINT = "3cb385a6a1ff316445ee6c4788ebfca0955d1253"
 
 
 def _function_text(src: str, name: str) -> str:
