@@ -181,8 +181,7 @@ struct exageo_ctx {
   // side stream (default priority) for the lookahead panel, and its events
   hipStream_t side = nullptr;
   hipEvent_t ev_col = nullptr, ev_panel = nullptr;
-  // stream (default priority) of the forward solve beside the factorisation,
-  // made by the first call with more than one tile
+  // stream (default priority) of the forward solve beside the factorisation
   hipStream_t fwd = nullptr;
   hipEvent_t ev_fwd = nullptr;
   // profiling
@@ -531,10 +530,6 @@ exageo_status factorize(exageo_ctx* c, const Plan& p, const double theta[3], boo
   double* rhs = at<double>(c, p.off_yv);
   double* yv = at<double>(c, p.off_y);
   const double* dinv = at<double>(c, p.off_dinv);
-  if (solve && p.NT > 1 && !c->ev_fwd) {
-    if (!c->fwd) HIPCHK(c, hipStreamCreateWithFlags(&c->fwd, hipStreamNonBlocking));
-    HIPCHK(c, hipEventCreateWithFlags(&c->ev_fwd, hipEventDisableTiming));
-  }
   hipStream_t S3 = c->fwd;
   if (solve) exg::launch_copy(rhs, at<double>(c, p.off_zs), p.npad, S);
   double* below = panel(0, S);
@@ -817,8 +812,10 @@ exageo_status exageo_create(exageo_ctx** out, int device, int64_t ts, void* hip_
   c->stream = (hipStream_t)hip_stream;
   if (hipSetDevice(device) != hipSuccess || hipHostMalloc((void**)&c->hres, 64 * sizeof(double)) != hipSuccess ||
       hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking) != hipSuccess ||
+      hipStreamCreateWithFlags(&c->fwd, hipStreamNonBlocking) != hipSuccess ||
       hipEventCreateWithFlags(&c->ev_col, hipEventDisableTiming) != hipSuccess ||
       hipEventCreateWithFlags(&c->ev_panel, hipEventDisableTiming) != hipSuccess ||
+      hipEventCreateWithFlags(&c->ev_fwd, hipEventDisableTiming) != hipSuccess ||
       exg::scratch_address(device, &c->scratch) != hipSuccess) {
     exageo_destroy(c);
     return EXAGEO_EDEVICE;
