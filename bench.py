@@ -649,11 +649,9 @@ def main() -> int:
         "potrf_frac_of_fp64_mfma_peak": chol_tflops / FP64_MFMA_PEAK_TFLOPS,
         "phases_ms": {k: avg(k) for k in ("prep_ms", "gen_ms", "chol_ms", "solve_ms", "grad_ms", "total_ms")},
         "gen_bessel_evals_per_s": (n * (n + 1) / 2) / (avg("gen_ms") * 1e-3),
-        # generation writes the lower tiles once; the forward solve reads them once
+        # generation writes the lower tiles once
         "gen_hbm_write_gbs": ((n + ts - 1) // ts) * (((n + ts - 1) // ts) + 1) / 2 * ts * ts * 8
                              / (avg("gen_ms") * 1e-3) / 1e9,
-        "solve_hbm_read_gbs": ((n + ts - 1) // ts) * (((n + ts - 1) // ts) + 1) / 2 * ts * ts * 8
-                              / (avg("solve_ms") * 1e-3) / 1e9,
         "loglik": lls[-1][0],
         "grad": lls[-1][1],
     }

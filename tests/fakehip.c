@@ -22,8 +22,10 @@ void fakehip_mark(const char *what) {
 }
 
 static int handle(void **p, const char *what) {
+  char line[64];
   *p = (void *)(handles++);
-  fakehip_mark(what);
+  snprintf(line, sizeof line, "%s %p", what, *p);
+  fakehip_mark(line);
   return 0;
 }
 static int memory(void **p, size_t n, const char *what) {
@@ -49,7 +51,12 @@ int hipStreamWaitEvent(void *s, void *e, unsigned f) { (void)s; (void)e; (void)f
 int hipEventCreate(void **e) { return handle(e, "hipEventCreate"); }
 int hipEventCreateWithFlags(void **e, unsigned f) { (void)f; return handle(e, "hipEventCreateWithFlags"); }
 int hipEventDestroy(void *e) { (void)e; fakehip_mark("hipEventDestroy"); return 0; }
-int hipEventRecord(void *e, void *s) { (void)e; (void)s; fakehip_mark("hipEventRecord"); return 0; }
+int hipEventRecord(void *e, void *s) {
+  char line[64];
+  snprintf(line, sizeof line, "hipEventRecord %p %p", e, s);
+  fakehip_mark(line);
+  return 0;
+}
 int hipEventSynchronize(void *e) { (void)e; return 0; }
 int hipEventElapsedTime(float *ms, void *a, void *b) { (void)a; (void)b; *ms = 0; return 0; }
 int hipMemcpy(void *d, const void *s, size_t n, int k) { (void)k; memcpy(d, s, n); fakehip_mark("hipMemcpy"); return 0; }

@@ -2,6 +2,7 @@
 stand-in for the HIP runtime (fakehip.c) that runs no kernel and writes every
 call to a file.  In a process of its own, so that nothing else binds to it."""
 import os
+import re
 import subprocess
 import sys
 
@@ -60,3 +61,30 @@ assert lib.exageo_loglik_grad_noalloc(ctx, *field({n}), theta, ctypes.byref(ll),
     assert any("k_potrf_blk" in c for c in inside) and inside[-1] == "hipStreamSynchronize"
     made = [c for c in inside if c.startswith("hip") and any(w in c for w in ("Malloc", "Free", "Create", "Destroy"))]
     assert made == []
+
+
+# the phases of exageo_get_timings: five tiles, so four are solved before the
+# event that ends the Cholesky phase and one after it; bench.py takes no rate
+# from the phase of the last one
+def test_forward_solve_in_the_phases(calls):
+    log = calls("""
+create(256)
+assert lib.exageo_set_profiling(ctx, 1) == 0
+mark("call")
+assert lib.exageo_loglik_grad(ctx, *field(1100), theta, 0, ctypes.byref(ll), grad, ctypes.byref(info)) == 0
+""")
+    ev = [c.split()[1] for c in log if c.startswith("hipEventCreate ")]
+    rec = [next(i for i, c in enumerate(log) if c.startswith(f"hipEventRecord {e} ")) for e in ev[:6]]
+    assert rec == sorted(rec) and rec[0] > log.index("call")
+
+    def launched(name, phase):  # between the events that bound it
+        return sum(name in c for c in log[rec[phase - 1]:rec[phase]])
+
+    assert [launched("k_potrf_blk", p) for p in range(1, 6)] == [0, 0, 9, 0, 0]
+    assert [launched("k_tile_fwd", p) for p in range(1, 6)] == [0, 0, 4, 1, 0]
+    assert launched("k_copy_diag_lower", 5) == 1  # FP64: the diagonal tiles' inverses
+    root = os.path.dirname(HERE)
+    header = " ".join(open(os.path.join(root, "include", "exageo.h")).read().replace("*", " ").split())
+    assert "forward solve of every tile but the last" in header and "forward solve of the last tile" in header
+    rates = re.findall(r'/ *\(avg\("(\w+)"\)', open(os.path.join(root, "bench.py")).read())
+    assert "gen_ms" in rates and "solve_ms" not in rates
