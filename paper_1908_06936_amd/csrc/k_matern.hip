@@ -48,6 +48,11 @@ __global__ void k_quad_table(double s2, double beta, double nu, double metric, d
     cst[C_METRIC] = metric;
     cst[C_NUG] = nugget;
     cst[C_RBETA] = 1.0 / beta;
+    int se, be;
+    frexp(s2, &se);
+    frexp(beta, &be);
+    cst[C_S2E] = __longlong_as_double(se);
+    cst[C_D1E] = __longlong_as_double(se - be);
     if (info) *info = ~0ull;
   }
 }
@@ -126,12 +131,13 @@ __global__ __launch_bounds__(256) void k_cheb_table(double* __restrict__ qt, con
   __syncthreads();
   if (t < 3 * 16) {
     const int f = t >> 4, k = t & 15;
-    const double A = cst[C_S2C] * fv[f][CH_MID];
+    int e;
+    const double A = frexp(cst[C_S2], &e) * cst[C_C] * fv[f][CH_MID];
     double c = 0.0;
     if (k < CH_A) {  // coefficient of t^(k + 1), the small terms first
       for (int q = CH_N - 1; q > k; --q) c = fma((double)CH_POW.t[q][k + 1], ch[f][q], c);
     } else if (k == CH_A) {
-      c = f == 1 ? A / cst[C_BETA] : A;
+      c = f == 1 ? A / frexp(cst[C_BETA], &e) : A;
     } else if (k == CH_A + 1) {
       c = cst[C_C] * fv[f][CH_MID];
     }

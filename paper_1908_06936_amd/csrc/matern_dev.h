@@ -68,7 +68,10 @@ constexpr int CH_STRIDE = 14;     // doubles per function and segment
 constexpr int CH_TAB = CH_NSEG * CH_STRIDE;  // doubles per function: u0, u1, u2 in turn
 constexpr int CH_MID = 6;         // the middle Chebyshev point, t = 0
 // per segment: the coefficients of t, ..., t^12, then the factors
-//   u0: sigma2 c u(centre), c u(centre);  u1: sigma2 c u(centre) / beta;  u2: sigma2 c u(centre)
+//   u0: s c u(centre), c u(centre);  u1: s c u(centre) / b;  u2: s c u(centre)
+// with s and b the mantissas of sigma2 and beta: c u(centre) reaches 1e26 (nu = 15),
+// so sigma2 itself would overflow it where the entry, e^-x smaller, does not.
+// The exponents join the entry's last scaling (C_S2E, C_D1E), which changes no bit.
 constexpr int CH_A = CH_N - 1;
 constexpr double CH_SLO = -23.0;  // ln x of the first segment's left end
 constexpr double CH_DS = 0.25;    // segment width in ln x
@@ -76,7 +79,9 @@ constexpr int QT_CHEB_OFF = QNB * QNK * QW;
 constexpr int QT_TOTAL = QT_CHEB_OFF + 3 * CH_TAB;
 
 // per-theta constants written by the table kernel
-enum { C_S2 = 0, C_BETA, C_NU, C_C, C_PSI, C_S2C, C_METRIC, C_NUG, C_RBETA, C_COUNT = 16 };
+// C_S2E, C_D1E: exponents of sigma2 and of sigma2 / beta (integers, see cst_int)
+enum { C_S2 = 0, C_BETA, C_NU, C_C, C_PSI, C_S2C, C_METRIC, C_NUG, C_RBETA, C_S2E, C_D1E, C_COUNT = 16 };
+__device__ __forceinline__ int cst_int(const double* __restrict__ cst, int i) { return __double2loint(cst[i]); }
 
 constexpr double EARTH_RADIUS_KM = 6371.0;
 
@@ -200,8 +205,8 @@ __device__ __forceinline__ double seg_poly(const double* __restrict__ b, double 
   return a * t;
 }
 
-// exp(p - x - xl), |p| < 10, 0 < x <= XMAX, xl below an ulp of x
-__device__ __forceinline__ double exp_diff(double p, double x, double xl) {
+// exp(p - x - xl) = m 2^*e, m in (0.7, 1.42), |p| < 10, 0 < x <= XMAX, xl below an ulp of x
+__device__ __forceinline__ double exp_diff(double p, double x, double xl, int* e) {
   const double hi = p - x, bb = hi - p, lo = (p - (hi - bb)) - (x + bb) - xl;
   const double k = rint(hi * 0x1.71547652b82fep+0);
   const double r = fma(-k, LN2L, fma(-k, LN2H, hi)) + lo;
@@ -215,7 +220,8 @@ __device__ __forceinline__ double exp_diff(double p, double x, double xl) {
   q = fma(q, r, 0x1.5555555553d61p-5);
   q = fma(q, r, 0x1.5555555555556p-3);
   q = fma(q, r, 0.5);
-  return ldexp(fma(r * r, q, r) + 1.0, (int)k);
+  *e = (int)k;
+  return fma(r * r, q, r) + 1.0;
 }
 
 // the covariance and its derivatives by the quadrature, x < XMIN (or NaN)
@@ -257,11 +263,11 @@ __device__ __forceinline__ double matern_value(double r, const double* __restric
     return quad_value(x, cst, qt);
   }
   const double xc = fmin(fmax(x, XMIN), XMAX);
-  int seg;
+  int seg, e;
   double t, lx;
   ln_locate(xc, &seg, &t, &lx);
   const double* b = tab + seg * CH_STRIDE;
-  const double v = b[CH_A] * exp_diff(seg_poly(b, t), xc, xl);
+  const double m = exp_diff(seg_poly(b, t), xc, xl, &e), v = ldexp(b[CH_A] * m, e + cst_int(cst, C_S2E));
   return r == 0.0 ? cst[C_S2] : (x > XMAX ? 0.0 : v);
 }
 
@@ -277,16 +283,17 @@ __device__ __forceinline__ void matern_grad(double r, const double* __restrict__
     return;
   }
   const double xc = fmin(fmax(x, XMIN), XMAX);
-  int seg;
+  int seg, i0, i1, i2;
   double t, lx;
   ln_locate(xc, &seg, &t, &lx);
   const double *b0 = tab + seg * CH_STRIDE, *b1 = b0 + CH_TAB, *b2 = b1 + CH_TAB;
   const bool at0 = r == 0.0, far = x > XMAX;
-  const double e0 = exp_diff(seg_poly(b0, t), xc, xl), e1 = exp_diff(seg_poly(b1, t), xc, xl),
-               e2 = exp_diff(seg_poly(b2, t), xc, xl);
+  const double m0 = exp_diff(seg_poly(b0, t), xc, xl, &i0), m1 = exp_diff(seg_poly(b1, t), xc, xl, &i1),
+               m2 = exp_diff(seg_poly(b2, t), xc, xl, &i2);
+  const double e0 = ldexp(m0, i0), e2 = ldexp(m2, i2);
   *d0 = at0 ? 1.0 : (far ? 0.0 : b0[CH_A + 1] * e0);
-  *d1 = at0 || far ? 0.0 : b1[CH_A] * e1;
-  *d2 = at0 || far ? 0.0 : fma(b0[CH_A] * e0, lc + lx, b2[CH_A] * e2);
+  *d1 = at0 || far ? 0.0 : ldexp(b1[CH_A] * m1, i1 + cst_int(cst, C_D1E));
+  *d2 = at0 || far ? 0.0 : ldexp(fma(b0[CH_A] * e0, lc + lx, b2[CH_A] * e2), cst_int(cst, C_S2E));
 }
 
 }  // namespace exg

@@ -179,3 +179,26 @@ def test_simulate_shares(orc, exa, n, ts):
     assert z @ np.linalg.solve(orc.matern_cov(x, y, th), z) == pytest.approx(e @ e, rel=1e-9)
     other = exa.Context(ts=384).simulate(dev(x), dev(y), th, dev(e)).cpu().numpy()
     np.testing.assert_allclose(z, other, rtol=0, atol=1e-9 * np.abs(e).max())
+
+
+# sigma2 and beta by powers of two: entries (exactly) and score scale with them, also
+# where sigma2 (or sigma2 / beta) times the table's largest factor, x^nu e^x
+# K_nu(x) near x = 700, would overflow
+@pytest.mark.parametrize("ks,kb", [(950, 0), (-950, 0), (500, -500)])
+@pytest.mark.parametrize("nu", [0.5, 2.0, 14.5])
+def test_entries_and_score_scale_by_powers_of_two(exa, nu, ks, kb):
+    ctx = exa.Context(ts=128)
+    x = np.array([0.0, 0.25, 1.0, 3.0, 10.0, 40.0, 400.0, 640.0, 690.0, 699.0])
+    y, th, big = np.zeros_like(x), [1.0, 1.0, nu], [2.0 ** ks, 2.0 ** kb, nu]
+    X = dev(np.ldexp(x, kb))
+    if kb == 0:
+        a = ctx.matern_cov(dev(x), dev(y), th).cpu().numpy()
+        b = ctx.matern_cov(X, dev(y), big).cpu().numpy()
+        np.testing.assert_array_equal(b, np.ldexp(a, ks))
+    ctx.set_nugget(0.1)
+    z = np.cos(np.arange(x.size))
+    l0, g0 = ctx.loglik_grad(dev(x), dev(y), dev(z), th)
+    ctx.set_nugget(0.1 * 2.0 ** ks)
+    l1, g1 = ctx.loglik_grad(X, dev(y), dev(np.ldexp(z, ks // 2)), big)
+    assert l1 == pytest.approx(l0 - 0.5 * x.size * ks * np.log(2.0), rel=1e-13)
+    assert_score_close([g1[0] * 2.0 ** ks, g1[1] * 2.0 ** kb, g1[2]], g0, x.size, th)
