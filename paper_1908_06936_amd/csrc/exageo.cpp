@@ -89,9 +89,11 @@ Plan make_plan(int64_t n, int64_t ts, int want_grad, int precision = EXAGEO_FP64
   p.off_xd = take((size_t)p.NT * tt * 8);
   // FP64 inverse: FP64 staging buffer (the mixed inverse stages in the FP32 panel copy)
   // (two halves: consecutive TRTRI steps stage on different streams); kriging
-  // uses it for its blocks of at least 128 new points (2 npad 128 doubles)
+  // uses it for its blocks of at least 128 new points (2 npad 128 doubles), and
+  // the score's contraction for its partial triples once the inverse is done
   if (p.grad && !p.mixed) {
     p.ptmp_doubles = std::max(2 * (size_t)std::max<int64_t>(1, p.NT - 1) * tt, 2 * (size_t)p.npad * BLKH);
+    p.ptmp_doubles = std::max(p.ptmp_doubles, 3 * (size_t)exg::lauum_blocks(ts, p.NT, exg::lauum_tiles(n)));
     p.off_ptmp = take(p.ptmp_doubles * 8);
   }
   p.off_dinv = take((size_t)p.NT * p.T * BLKH * BLKH * 8);
@@ -109,7 +111,8 @@ Plan make_plan(int64_t n, int64_t ts, int want_grad, int precision = EXAGEO_FP64
   p.off_box = take(8 * 8);
   p.off_qt = take((size_t)exg::quad_table_doubles() * 8);
   p.off_cst = take(16 * 8);
-  p.off_part = take((size_t)(p.grad ? exg::lauum_blocks(ts, p.NT) + p.pool_cap * p.T * p.T : 1) * 3 * 8);
+  // partial triples of the mixed score (128 x 128 blocks, the FP64 band's after the others')
+  if (p.grad && p.mixed) p.off_part = take((size_t)(exg::lauum_blocks(ts, p.NT, 4) + p.pool_cap * p.T * p.T) * 3 * 8);
   p.off_out = take(16 * 8);
   p.off_info = take(8);
   if (want_grad >= 2 && !p.mixed) {
@@ -702,7 +705,7 @@ exageo_status gradient(exageo_ctx* c, const Plan& p) {
   double* av = at<double>(c, p.off_alpha);
   double* Xd = p.mixed ? at<double>(c, p.off_xd) : diag_inverses(c, p);  // mixed: formed for the solve
   int64_t nparts = 0;  // partial triples of the contraction
-  double* part = at<double>(c, p.off_part);
+  double* part = nullptr;
   const int64_t tt = p.ts * p.ts, half = std::max<int64_t>(1, p.NT - 1) * tt;
   // a = Sigma^-1 z = L^-T y (already there, refined, in mixed precision with
   // refinement steps)
@@ -727,6 +730,7 @@ exageo_status gradient(exageo_ctx* c, const Plan& p) {
           exg::launch_trtri_rest_lp(M, tag, Xd + k * tt, P32 + (k & 1) * half, Q64 + (k & 1) * half, bl, k, p.n, s);
         });
     if (st) return st;
+    part = at<double>(c, p.off_part);
     nparts = exg::launch_lauum_contract_lp(M, tag, p.n, at<double>(c, p.off_xs), at<double>(c, p.off_ys), av,
                                            at<double>(c, p.off_qt), at<double>(c, p.off_cst),
                                            at<int32_t>(c, p.off_bli), at<int32_t>(c, p.off_blj), c->bfirst[p.NT],
@@ -740,10 +744,7 @@ exageo_status gradient(exageo_ctx* c, const Plan& p) {
         [&](int64_t k, hipStream_t s) { exg::launch_trtri_right(M, Xd + k * tt, P64 + (k & 1) * half, k, p.n, s); },
         [&](int64_t k, hipStream_t s) { exg::launch_trtri_rest(M, Xd + k * tt, P64 + (k & 1) * half, k, p.n, s); });
     if (st) return st;
-    // the staging buffer is free again and holds the partial triples of any
-    // block size: 2 (NT - 1) ts^2 doubles (2 ts^2 for one tile) against
-    // 3 (NT (NT + 1) / 2) (ts / 32)^2
-    part = P64;
+    part = P64;  // the staging buffer is free again
     nparts = exg::launch_lauum_contract(M, p.n, at<double>(c, p.off_xs), at<double>(c, p.off_ys), av,
                                         at<double>(c, p.off_qt), at<double>(c, p.off_cst), part, c->stream);
   }

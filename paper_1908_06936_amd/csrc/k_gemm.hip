@@ -455,17 +455,12 @@ void launch_trtri_rest(const TileMat& M, const double* Xk, double* P, int64_t k,
   launch_copy(M.diag + k * tt, Xk, tt, s);
 }
 
-int64_t lauum_blocks(int64_t ts, int64_t NT) { return NT * (NT + 1) / 2 * (ts / BLK) * (ts / BLK); }
-
-// The block edge follows the number of blocks with real entries (the padded
-// ones end at once).  Returns the number of partial triples written.
 int64_t launch_lauum_contract(const TileMat& M, int64_t nreal, const double* xs, const double* ys, const double* av,
                               const double* qt, const double* cst, double* part, hipStream_t s) {
   const int64_t t64 = M.ts / TB, npt = t64 * (t64 + 1) / 2, ntr = M.NT * (M.NT + 1) / 2 * npt;
   hipLaunchKernelGGL(k_transpose_tiles, dim3((unsigned)ntr), dim3(256), 0, s, M, npt, ntr);
-  const int64_t R = (nreal + BLK - 1) / BLK;
-  const int B = block_tiles_uneven(R * (R + 1) / 2);
-  const int64_t T = M.ts / (32 * B), nb = M.NT * (M.NT + 1) / 2 * T * T;
+  const int B = lauum_tiles(nreal);
+  const int64_t T = M.ts / (32 * B), nb = lauum_blocks(M.ts, M.NT, B);
   const int ch = xcd_chunk_size(B, (int)T, nb);
   EXG_BLOCKS(B, k_lauum_contract, xcd_chunk_grid(nb, ch), s, M, (int)T, nreal, xs, ys, av, qt, cst, part, nb, ch);
   return nb;

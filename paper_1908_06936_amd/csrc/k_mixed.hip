@@ -994,7 +994,7 @@ void launch_trtri_rest_lp(const TileMat& M, const uint8_t* tag, const double* Xk
   launch_copy(M.diag + k * tt, Xk, tt, s);
 }
 
-// part: lauum_blocks(ts, NT) + nband T^2 triples, the FP32 blocks first;
+// part: lauum_blocks(ts, NT, 4) + nband T^2 triples, the FP32 blocks first;
 // returns the number of triples written
 int64_t launch_lauum_contract_lp(const TileMat& M, const uint8_t* tag, int64_t nreal, const double* xs,
                                  const double* ys, const double* av, const double* qt, const double* cst,

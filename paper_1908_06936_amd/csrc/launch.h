@@ -186,9 +186,18 @@ void launch_diag_inverses(double* Xd, const double* diag, const double* dinv, in
 // the step's two halves: P_k and column k (any stream), then the rest
 void launch_trtri_right(const TileMat& M, const double* Xk, double* P, int64_t k, int64_t nreal, hipStream_t s);
 void launch_trtri_rest(const TileMat& M, const double* Xk, double* P, int64_t k, int64_t nreal, hipStream_t s);
-int64_t lauum_blocks(int64_t ts, int64_t NT);  // 128 x 128 blocks of the lower tiles
-// part: three doubles for each 32 x 32 block of the lower tiles at most;
-// returns the number of partial triples written
+// edge (in 32s) of the output blocks of the fused LAUUM and contraction, by the
+// number of 128 x 128 blocks with real entries, and the blocks of the lower tiles
+inline int lauum_tiles(int64_t nreal) {
+  const int64_t R = (nreal + BLK - 1) / BLK;
+  return block_tiles_uneven(R * (R + 1) / 2);
+}
+inline int64_t lauum_blocks(int64_t ts, int64_t NT, int B) {
+  const int64_t T = ts / (32 * B);
+  return NT * (NT + 1) / 2 * T * T;
+}
+// part: 3 lauum_blocks(ts, NT, lauum_tiles(nreal)) doubles; returns the number of
+// partial triples written
 int64_t launch_lauum_contract(const TileMat& M, int64_t nreal, const double* xs, const double* ys, const double* av,
                            const double* qt, const double* cst, double* part, hipStream_t s);
 

@@ -61,6 +61,23 @@ def test_workspace_bytes_host_only(lib):
     assert 0.9 * a < m < 1.25 * a
 
 
+@pytest.mark.parametrize("n,ts", [(100, 128), (700, 768), (4000, 256), (10000, 512), (10000, 128), (40000, 768)])
+def test_workspace_of_the_score(lib, n, ts):
+    # over l alone, the FP64 score takes one staging buffer: two halves of the
+    # inverse, blocks of 128 new points, or the contraction's partial triples
+    # (128-, 64- or 32-wide blocks by the number of 128-blocks with real entries)
+    from paper_1908_06936_amd._lib import FP64
+
+    nt = -(-n // ts)
+    r = -(-n // 128)
+    nb = r * (r + 1) // 2
+    edge = 128 if nb >= 1536 else (64 if nb >= 64 else 32)
+    triples = nt * (nt + 1) // 2 * (ts // edge) ** 2
+    doubles = max(2 * max(1, nt - 1) * ts * ts, 2 * nt * ts * 128, 3 * triples)
+    ws = lib.exageo_workspace_bytes
+    assert ws(n, ts, FP64, 1) - ws(n, ts, FP64, 0) == -(-doubles * 8 // 256) * 256
+
+
 def test_workspace_of_the_fisher_information(lib):
     # the derivative matrices take one buffer of lower tiles each (npad^2 / 2
     # doubles), two without a nugget and three with one, plus a strip of about
