@@ -158,6 +158,59 @@ def test_tile_index_reciprocal_is_exact_in_range():
         assert np.array_equal(got, a // np.uint64(d)), d
 
 
+def test_xcd_chunks_visit_every_block_once(tmp_path):
+    # the launch rule (xcd_chunk_size, xcd_chunk_grid) and the kernels' mapping
+    # (xcd_chunk), compiled for the host from the sources' own text: over block
+    # counts around the threshold, of whole and of ragged chunks, every block of
+    # the launch is formed by one workgroup, and the rule takes all three chunks
+    import subprocess
+
+    csrc = os.path.join(ROOT, "paper_1908_06936_amd", "csrc")
+
+    def function(name, head):
+        text = open(os.path.join(csrc, name)).read()
+        at = text.index(head)
+        return text[at:text.index("\n}\n", at) + 3]
+
+    src = """
+#include <cstdint>
+#include <cstdio>
+#include <vector>
+#define __device__
+#define __forceinline__ inline
+static struct { uint32_t x; } blockIdx;
+""" + function("common.h", "__device__ __forceinline__ int64_t xcd_chunk(") + function(
+        "launch.h", "inline int xcd_chunk_size(") + function("launch.h", "inline int64_t xcd_chunk_grid(") + """
+int main() {
+  int whole = 0, row = 0, plain = 0;
+  for (int T = 1; T <= 32; ++T)
+    for (int64_t p = 1; p * T * T <= 40000; p += p * T * T < 3500 ? (p + 7) / 8 * 8 : 1 + 97 / (T * T)) {
+      const int64_t nb = p * T * T;
+      const int ch = xcd_chunk_size(4, T, nb);
+      const int64_t grid = xcd_chunk_grid(nb, ch);
+      std::vector<int> seen(nb);
+      for (int64_t g = 0; g < grid; ++g) {
+        blockIdx.x = (uint32_t)g;
+        const int64_t b = xcd_chunk(nb, ch);
+        if (b < -1 || b >= nb) return 1;
+        if (b >= 0) ++seen[b];
+      }
+      for (int64_t b = 0; b < nb; ++b)
+        if (seen[b] != 1) return 2;
+      if (nb < 4096 && ch != 1) return 3;
+      if (T > 1) (ch == T * T ? whole : ch == T ? row : plain) += nb >= 4096;
+    }
+  std::printf("%d %d %d\\n", whole, row, plain);
+  return !(whole && row && plain);
+}
+"""
+    cpp, exe = tmp_path / "xcd.cpp", tmp_path / "xcd"
+    cpp.write_text(src)
+    subprocess.run(["g++", "-O2", "-std=c++17", str(cpp), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, (r.returncode, r.stdout)
+
+
 def test_profile_summaries_state_runnable_commands():
     # every committed rocprofv3 summary gives the command that made it; the
     # profiled program is the committed bench.py and every option it passes

@@ -141,6 +141,26 @@ def test_block_orders_over_the_xcds(exa, n, ts):
     assert_score_close(g, g_ref, n, th)
 
 
+# the same at sizes from which the trailing update, the inverse's update and the
+# mixed inverse's update take whole tiles (ts = 256 and 768) and, at ts = 768 and in
+# the contraction there, rows of a tile as chunks; the mixed score against FP64 at
+# the 1e-6 that the default map is held to
+@pytest.mark.parametrize("n,ts", [(17001, 256), (18601, 768)])
+def test_block_orders_of_every_chunked_launch(exa, n, ts):
+    x, y = inputgen.uniform(n, seed=900 + ts)
+    z = inputgen.smooth_field(x, y, seed=n)
+    th = [1.0, 0.02, 0.5]
+    X, Y, Z = dev(x), dev(y), dev(z)
+    ctx = exa.Context(ts=ts)
+    ll, g = ctx.loglik_grad(X, Y, Z, th)
+    ll_ref, g_ref = exa.Context(ts=128).loglik_grad(X, Y, Z, th)
+    assert ll == pytest.approx(ll_ref, rel=1e-10)
+    assert_score_close(g, g_ref, n, th)
+    lm, gm = ctx.loglik_grad(X, Y, Z, th, "mixed")
+    assert lm == pytest.approx(ll_ref, rel=1e-6)
+    assert np.abs(np.subtract(gm, g_ref)).max() <= 1e-6 * np.abs(g_ref).max()
+
+
 # entries at the ends of the table and of the fast forms: distances below and
 # above e^-23 beta and 700 beta, zero, squares that overflow and nearly vanish,
 # and ranges outside the short division, against the closed forms of nu = 1/2
