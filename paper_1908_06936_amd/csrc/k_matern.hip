@@ -158,11 +158,10 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
 // NULL): diagonal tiles FP64, off-diagonal tiles FP32 (tag 0) or BF16 (tag 1),
 // each rounded to nearest even from the FP64 value, or FP64 in the band pool
 // (tag 2).  A block's columns are shared by `parts` workgroups: 1 where the
-// blocks fill the chip, 8 where they would not (n = 400, 16 real blocks: 73 us
-// with 64 entries one after another in each thread, 11 us with 8).  Bound by the
-// entries' instructions and table reads (matern_dev.h): n = 40,000 in 6.0 ms,
-// 1.3e11 entries/s and 1.1 TB/s written.  Tiles
-// outside the DST band are zero and are written only if fill_zero.
+// blocks fill the chip, 8 where they would not.  Bound by the entries'
+// instructions and table reads (matern_dev.h): n = 40,000 in 6.0 ms, 1.3e11
+// entries/s and 1.1 TB/s written.  Tiles outside the DST band are zero and are
+// written only if fill_zero.
 __global__ __launch_bounds__(256) void k_gen_tiles(TileMat M, int T, int64_t nreal, const double* __restrict__ xs,
                                                    const double* __restrict__ ys, const double* __restrict__ qt,
                                                    const double* __restrict__ cst, const uint8_t* __restrict__ tag,
@@ -245,7 +244,10 @@ void launch_gen_tiles(const TileMat& M, int64_t nreal, const double* xs, const d
   const int64_t ts = M.ts, NT = M.NT;
   const int T = (int)(ts / BLK);
   const int64_t ntile = NT * (NT + 1) / 2;
-  const int64_t R = (nreal + BLK - 1) / BLK;  // 128-blocks with real rows
+  // 1 and 8 workgroups per block of the R (R + 1) / 2 with real rows: n = 400 56 and
+  // 11 us, n = 4,096 (528 blocks) 84 and 66, n = 6,400 (1,275) 141 and 131, n = 8,100
+  // (2,080) 195 and 199, n = 10,000 287 and 302, n = 20,000 991 and 1,163
+  const int64_t R = (nreal + BLK - 1) / BLK;
   const int parts = R * (R + 1) / 2 < 2048 ? 8 : 1;
   // keep each launch's grid below 2^31 blocks
   const int64_t per = ((int64_t)1 << 30) / (T * T * parts);

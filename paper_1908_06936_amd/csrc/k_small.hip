@@ -140,7 +140,7 @@ __global__ void k_gather(const double* __restrict__ x, const double* __restrict_
 }
 
 // rank[i] += number of keys among RT of them (block y's) below key i.  The keys
-// are distinct, so the ranks are the places in the sorted order.  n^2 / 2 key
+// are distinct, so the ranks are the places in the sorted order.  n^2 key
 // comparisons, but one launch: the bitonic network's launches are bound by
 // latency (n = 400: 28 us in one workgroup; n = 10,000: ten launches, 64 us).
 constexpr int RT = 512;

@@ -19,6 +19,19 @@ namespace exg {
 // trailing updates at n = 1,600 (36 blocks) 109 us, 35 us; (l, grad) at
 // n = 1,600 3,527 us, 1,823 us; DST l at n = 40,000, 4 tiles wide, 48.5 ms,
 // 26.8 ms.
+// The weights 1.15 and 1.6 prefer the wider block where the rounds are close.
+// They are high: of one launch of 7,440 blocks (n = 16,384, tile 512) 64- and
+// 32-wide ones take 0.97 and 1.11 times as long as 128-wide ones, since two or
+// more workgroups share a CU and the rounds blur.  All launches of one call on
+// 128-, 64- and 32-wide blocks, by the rule, and the best of each launch, us:
+//   trailing update     n = 10,000  6,795  5,521  5,748   5,865   5,426
+//                       n = 16,384 24,130 22,047 24,396  23,069  21,965
+//   inverse's update    n = 10,000  5,975  5,272  6,025   5,828   5,254
+//   (tile 768)          n = 20,000 39,268 41,361 46,325  39,268  38,915
+//   panel update        n = 16,384  7,663  2,206  1,595   1,973   1,529
+//   panel solve         n = 16,384  7,116  2,766  1,517   2,509   1,517
+// The last is where the rule is worst: from 33 to 64 blocks it takes 64-wide
+// ones (14 us) where 32-wide ones have 10.
 inline int block_tiles(int64_t nb) {
   const double c4 = (double)((nb + 255) / 256), c2 = 1.15 * 0.25 * (double)((4 * nb + 255) / 256),
                c1 = 1.6 * 0.0625 * (double)((16 * nb + 255) / 256);
@@ -26,9 +39,19 @@ inline int block_tiles(int64_t nb) {
 }
 
 // The same where the k range differs from block to block (the longest ones
-// decide): 128 x 128 only where several rounds even it out.  Fisher products
-// at n = 6,400 (about 400 blocks a launch): xg 1,159 us on 128 x 128, 656 us
-// on 64 x 64 blocks.
+// decide): 128 x 128 only where several rounds even it out.  One launch on 128-,
+// 64- and 32-wide blocks, us:
+//   fused LAUUM, tile 512   n =   640    15 blocks    194     60     30
+//                           n = 1,408    66 blocks    263     86     63
+//                           n = 2,560   210 blocks    401    191    194
+//                           n = 4,608   666 blocks    874    762    833
+//                           n = 6,400 1,275 blocks  2,029  2,028  2,269
+//                           n = 8,192 2,080 blocks  3,541  3,701  4,359
+//                           n = 14,000 6,105 blocks 15,826 18,286 21,728
+// so the upper line lies where 64 and 128 cross; the lower one could lie at 200.
+// Fisher products of a call (400 to 900 blocks a launch): xg at n = 6,400 14.2,
+// 8.0 and 9.2 ms, at n = 12,000 48.5, 41.2 and 56.8; mxt at n = 6,400 8.8, 5.1 and
+// 5.5 ms.
 inline int block_tiles_uneven(int64_t nb) { return nb >= 1536 ? 4 : (nb >= 64 ? 2 : 1); }
 
 // Blocks per chunk of the XCD order (xcd_chunk) of a launch of nb blocks of one
