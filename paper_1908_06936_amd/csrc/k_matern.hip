@@ -86,7 +86,9 @@ __global__ __launch_bounds__(256) void k_cheb_table(double* __restrict__ qt, con
   __shared__ int nk[CH_N];
   const int seg = blockIdx.x, t = threadIdx.x;
   const double pi = 3.14159265358979323846;
-  const double nu = cst[C_NU];
+  const double nu = cst[C_NU], cnu = cst[C_C];
+  int e;
+  const double sc = frexp(cst[C_S2], &e) * cnu, bm = frexp(cst[C_BETA], &e);  // the mantissas'
   if (t < CH_N * CH_N) cs[t / CH_N][t % CH_N] = cos(pi * (t / CH_N) * (t % CH_N + 0.5) / CH_N);
   if (t < CH_N * LP) {
     const int j = t / LP, l = t % LP;
@@ -131,15 +133,14 @@ __global__ __launch_bounds__(256) void k_cheb_table(double* __restrict__ qt, con
   __syncthreads();
   if (t < 3 * 16) {
     const int f = t >> 4, k = t & 15;
-    int e;
-    const double A = frexp(cst[C_S2], &e) * cst[C_C] * fv[f][CH_MID];
+    const double A = sc * fv[f][CH_MID];
     double c = 0.0;
     if (k < CH_A) {  // coefficient of t^(k + 1), the small terms first
       for (int q = CH_N - 1; q > k; --q) c = fma((double)CH_POW.t[q][k + 1], ch[f][q], c);
     } else if (k == CH_A) {
-      c = f == 1 ? A / frexp(cst[C_BETA], &e) : A;
+      c = f == 1 ? A / bm : A;
     } else if (k == CH_A + 1) {
-      c = cst[C_C] * fv[f][CH_MID];
+      c = cnu * fv[f][CH_MID];
     }
     if (k < CH_STRIDE) qt[QT_CHEB_OFF + f * CH_TAB + seg * CH_STRIDE + k] = c;
   }
